@@ -26,13 +26,16 @@ __device__ __forceinline__ double rot_coef(const Geo& g, const LineCtx& lc, doub
 // nonlinear H).  The pointwise part goes with the x pass, where V is read contiguously; the
 // strided passes then read only f and the running sum.
 // ---------------------------------------------------------------------------------------------
+// Every input is read ahead of the first store: `acc` and `out` may be one buffer, so a read after a
+// store is a memory round trip of its own (the y pass took eight in a row: 2.7 of its 5.5 us on a
+// 256^2 FP64 field).
 template <typename T, int AX>
 struct OpApply {
-    static constexpr bool FWD = true, INV = true, SCALARS = false, PREFETCH = false, WIDE = false;
+    static constexpr bool FWD = true, INV = true, SCALARS = false, PREFETCH = true, WIDE = false;
     static constexpr int K = 0;
     static constexpr unsigned MAXMASK = 0;
     const C2<T>* f;
-    const C2<T>* acc;  // nullable
+    const C2<T>* acc;  // strided passes: the running sum (nullptr: none)
     C2<T>* out;
     const T* V;        // used by the pass with `pointwise` set
     double beta, omega;
@@ -40,13 +43,30 @@ struct OpApply {
     double kin = 1.0;  // weight of the kinetic symbol (0: rotation part only)
     // only the x pass carries the pointwise part: the strided passes keep no copy of f
     static constexpr bool PW = AX == 0;
-    struct State { C2<T> f0[PW ? 8 : 1]; };
-    __device__ void load(const Geo&, const LineCtx& lc, State& st, C2<T> (&v)[8], double (&acc)[K > 0 ? K : 1]) const {
+    struct State {
+        C2<T> f0[8];
+        C2<T> a[PW ? 1 : 8];
+        T V[PW ? 8 : 1];
+    };
+    __device__ void prefetch(const Geo&, const LineCtx& lc, State& st) const {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) st.f0[s] = f[lc.at(s)];
+    }
+    // the x pass starts the sum, the strided passes continue it
+    __device__ void prefetch_tail(const Geo&, const LineCtx& lc, State& st) const {
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
-            v[s] = f[lc.at(s)];
-            if constexpr (PW) st.f0[s] = v[s];
+            const int64_t i = lc.at(s);
+            if constexpr (PW) {
+                st.V[s] = pointwise && V ? V[i - lc.off_b] : (T)0;
+            } else {
+                st.a[s] = acc ? acc[i] : mk((T)0, (T)0);
+            }
         }
+    }
+    __device__ void load(const Geo&, const LineCtx&, State& st, C2<T> (&v)[8], double (&)[1]) const {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) v[s] = st.f0[s];
     }
     template <int LG>
     __device__ void spectral(const Geo& g, const LineCtx& lc, State&, C2<T> (&v)[8], double (&)[1], C2<T>*,
@@ -62,17 +82,17 @@ struct OpApply {
     __device__ void store(const Geo&, const LineCtx& lc, State& st, C2<T> (&v)[8], double (&)[1]) const {
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
-            const int64_t i = lc.at(s);
             C2<T> o = v[s];
-            if (acc) o = add(o, acc[i]);
             if constexpr (PW) {
                 if (pointwise && V) {
-                    T w = V[i - lc.off_b];
+                    T w = st.V[s];
                     if (nonlinear) w += (T)beta * abs2(st.f0[s]);
                     o = add(o, scl(st.f0[s], w));
                 }
+            } else {
+                o = add(o, st.a[s]);
             }
-            out[i] = o;
+            out[lc.at(s)] = o;
         }
     }
 };
@@ -185,10 +205,13 @@ struct OpProlong {
         C2<T>* o = out + 2 * lc.off_b;
         const int64_t e0 = 2 * (lc.at(0) - lc.off_b) - keep;  // the points of a thread are TPL apart
         const int64_t de = 2 * (int64_t)lc.TPL * lc.stride;
+        C2<T> f0[8];  // re-read (cached), ahead of the first store: keeping the inputs across the
+#pragma unroll      // transforms put them in scratch memory in FP64
+        for (int s = 0; s < 8; ++s) f0[s] = f[lc.at(s)];
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
-            o[e0 + s * de] = f[lc.at(s)];  // re-read (cached): keeping the inputs across the transforms
-            o[e0 + s * de + step] = v[s];  // put them in scratch memory in FP64
+            o[e0 + s * de] = f0[s];
+            o[e0 + s * de + step] = v[s];
         }
     }
 };
@@ -301,16 +324,29 @@ hipError_t op_autotune(const Geo& g, bool f64, int B, const Twiddles& tw, void* 
 // ---------------------------------------------------------------------------------------------
 template <typename T, int AX>
 struct OpEnergy {
-    static constexpr bool FWD = true, INV = false, SCALARS = false, PREFETCH = false, WIDE = false;
+    static constexpr bool FWD = true, INV = false, SCALARS = false, PREFETCH = true, WIDE = false;
     static constexpr int K = 4;
     static constexpr unsigned MAXMASK = 0;
     const C2<T>* phi;
     const T* V;
     double omega;
-    struct State { C2<T> f0[8]; };
-    __device__ void load(const Geo&, const LineCtx& lc, State& st, C2<T> (&v)[8], double (&acc)[K > 0 ? K : 1]) const {
+    struct State {
+        C2<T> f0[8];
+        T V[AX == 0 ? 8 : 1];
+    };
+    __device__ void prefetch(const Geo&, const LineCtx& lc, State& st) const {
 #pragma unroll
-        for (int s = 0; s < 8; ++s) st.f0[s] = v[s] = phi[lc.at(s)];
+        for (int s = 0; s < 8; ++s) st.f0[s] = phi[lc.at(s)];
+    }
+    __device__ void prefetch_tail(const Geo&, const LineCtx& lc, State& st) const {
+        if constexpr (AX == 0) {
+#pragma unroll
+            for (int s = 0; s < 8; ++s) st.V[s] = V[lc.at(s)];
+        }
+    }
+    __device__ void load(const Geo&, const LineCtx&, State& st, C2<T> (&v)[8], double (&)[K]) const {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) v[s] = st.f0[s];
     }
     template <int LG>
     __device__ void spectral(const Geo& g, const LineCtx& lc, State&, C2<T> (&v)[8], double (&acc)[4], C2<T>*,
@@ -325,14 +361,14 @@ struct OpEnergy {
             acc[1] += rot * xi * w;
         }
     }
-    __device__ void store(const Geo&, const LineCtx& lc, State& st, C2<T> (&)[8], double (&acc)[4]) const {
-        if (AX != 0) return;
+    __device__ void store(const Geo&, const LineCtx&, State& st, C2<T> (&)[8], double (&acc)[4]) const {
+        if constexpr (AX == 0) {
 #pragma unroll
-        for (int s = 0; s < 8; ++s) {
-            const int64_t i = lc.at(s);
-            const double r = (double)abs2(st.f0[s]);
-            acc[2] += (double)V[i] * r;
-            acc[3] += r * r;
+            for (int s = 0; s < 8; ++s) {
+                const double r = (double)abs2(st.f0[s]);
+                acc[2] += (double)st.V[s] * r;
+                acc[3] += r * r;
+            }
         }
     }
 };
@@ -414,9 +450,11 @@ __device__ __forceinline__ T pv_scale(int kind, double alpha, T V, T rho, double
 
 template <typename T, int AX, bool F, bool I>
 struct OpPre {
-    static constexpr bool FWD = F, INV = I, SCALARS = false, PREFETCH = false, WIDE = false;
+    static constexpr bool FWD = F, INV = I, SCALARS = false, PREFETCH = true, WIDE = false;
     static constexpr int K = 0;
     static constexpr unsigned MAXMASK = 0;
+    // only the x passes scale: the prologue's and the epilogue's V and phi (1-D does both)
+    static constexpr bool PRE = AX == 0 && F, POST = AX == 0 && I;
     const C2<T>* in;
     C2<T>* out;
     const C2<T>* phi;
@@ -424,14 +462,35 @@ struct OpPre {
     const double* alpha;
     double beta;
     int pre, post;
-    struct State {};
-    __device__ void load(const Geo&, const LineCtx& lc, State&, C2<T> (&v)[8], double (&acc)[K > 0 ? K : 1]) const {
-        const double a = *alpha;
+    struct State {
+        C2<T> f0[8], ph[PRE || POST ? 8 : 1];
+        T V[PRE || POST ? 8 : 1];
+    };
+    __device__ void scale_inputs(const LineCtx& lc, State& st) const {
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
             const int64_t i = lc.at(s);
-            v[s] = in[i];
-            if (pre) v[s] = scl(v[s], pv_scale<T>(pre, a, V[i], abs2(phi[i]), beta));
+            st.V[s] = V[i];
+            st.ph[s] = phi[i];
+        }
+    }
+    __device__ void prefetch(const Geo&, const LineCtx& lc, State& st) const {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) st.f0[s] = in[lc.at(s)];
+        if constexpr (PRE)
+            if (pre) scale_inputs(lc, st);
+    }
+    __device__ void prefetch_tail(const Geo&, const LineCtx& lc, State& st) const {
+        if constexpr (POST)
+            if (post && !(PRE && pre)) scale_inputs(lc, st);
+    }
+    __device__ void load(const Geo&, const LineCtx&, State& st, C2<T> (&v)[8], double (&)[1]) const {
+        const double a = *alpha;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            v[s] = st.f0[s];
+            if constexpr (PRE)
+                if (pre) v[s] = scl(v[s], pv_scale<T>(pre, a, st.V[s], abs2(st.ph[s]), beta));
         }
     }
     template <int LG>
@@ -456,14 +515,14 @@ struct OpPre {
             v[s] = scl(v[s], (T)(invN / (a + 0.5 * (ko + k * k))));
         }
     }
-    __device__ void store(const Geo&, const LineCtx& lc, State&, C2<T> (&v)[8], double (&)[1]) const {
+    __device__ void store(const Geo&, const LineCtx& lc, State& st, C2<T> (&v)[8], double (&)[1]) const {
         const double a = post ? *alpha : 0.0;
 #pragma unroll
         for (int s = 0; s < 8; ++s) {
-            const int64_t i = lc.at(s);
             C2<T> o = v[s];
-            if (post) o = scl(o, pv_scale<T>(post, a, V[i], abs2(phi[i]), beta));
-            out[i] = o;
+            if constexpr (POST)
+                if (post) o = scl(o, pv_scale<T>(post, a, st.V[s], abs2(st.ph[s]), beta));
+            out[lc.at(s)] = o;
         }
     }
 };
