@@ -2,6 +2,7 @@
 //   * H_phi phi and L f = (T + V - omega L_z) f            (Sections 2-3)
 //   * the energy E(phi) and its parts                     (Section 2)
 //   * the preconditioners P_Delta, P_V, P_C, P_C1, P_C2   (Section 5.5)
+#include <algorithm>
 #include <cmath>
 #include <vector>
 
@@ -97,35 +98,66 @@ struct OpApply {
     }
 };
 
+// Fields of one part of a batched apply.  The passes share phi and the running sum between launches;
+// when phi, the sum and the output of a whole batch exceed the 256 MB last-level cache, every pass
+// after the first takes them from HBM.  A batch is therefore applied in equal parts of at most
+// kApplyPartBytes of those three, which reuse one region for the sum.  Measured (us, whole batch;
+// parts of at most 100, 160, 230 MB): 64 x 512^2 FP32 165; 155, 147, 142.  32 x 512^2 FP64 142; 162,
+// 138, 130.  32 x 640^2 FP64 302; 376, 302, 286.  256 x 256^2 FP32 145; 142, 130, 125.  Three-pass
+// (3-D) batches gain little (4 x 128^3 FP64 196; 212, 211, 187).
+constexpr int64_t kApplyPartBytes = int64_t(224) << 20;
+static int apply_part(const Geo& g, int complex_bytes, int B) {
+    const int64_t field = 3 * (int64_t)complex_bytes * g.N;
+    const int64_t most = std::max<int64_t>(1, kApplyPartBytes / field);
+    const int64_t parts = (B + most - 1) / most;
+    return (int)((B + parts - 1) / parts);
+}
+
+// One part: B of the batch's fields.  Tiles follow the whole batch (Cx, Cy, Cz lines per workgroup).
+template <typename T>
+static hipError_t apply_part_t(const Geo& g, int B, const Twiddles& tw, const C2<T>* F, const T* V, C2<T>* out,
+                               C2<T>* tmp, double beta, double omega, bool nl, bool plane, const int C[3],
+                               hipStream_t s) {
+    const bool f64 = sizeof(T) == 8;
+    Partials none{nullptr, 0, 0, 0};
+    hipError_t e;
+    if (plane) {
+        // whole xy-planes in LDS, the xy-part into tmp, then the z pass
+        if ((e = op_apply_plane(g, f64, B, tw, F, V, tmp, beta, omega, nl, s)) != hipSuccess) return e;
+        OpApply<T, 2> oz{F, tmp, out, nullptr, beta, omega, 0, nl};
+        return launch_pass<T, 2>(g, B, tw.get(2, f64), oz, none, s, nullptr, C[2]);
+    }
+    // x-pass (with the pointwise part) into tmp, then the y (and z) passes accumulate.
+    OpApply<T, 0> ox{F, nullptr, tmp, V, beta, omega, 1, nl};
+    if ((e = launch_pass<T, 0>(g, B, tw.get(0, f64), ox, none, s, nullptr, C[0])) != hipSuccess) return e;
+    OpApply<T, 1> oy{F, tmp, g.dim == 2 ? out : tmp, nullptr, beta, omega, 0, nl};
+    if ((e = launch_pass<T, 1>(g, B, tw.get(1, f64), oy, none, s, nullptr, C[1])) != hipSuccess || g.dim == 2) return e;
+    OpApply<T, 2> oz{F, tmp, out, nullptr, beta, omega, 0, nl};
+    return launch_pass<T, 2>(g, B, tw.get(2, f64), oz, none, s, nullptr, C[2]);
+}
+
 template <typename T>
 static hipError_t apply_t(const Geo& g, int B, const Twiddles& tw, const void* f, const void* V, void* out,
                           void* tmp, double beta, double omega, bool nl, hipStream_t s) {
     const bool f64 = sizeof(T) == 8;
     const C2<T>* F = (const C2<T>*)f;
-    Partials none{nullptr, 0, 0, 0};
-    hipError_t e;
+    C2<T>* O = (C2<T>*)out;
     if (g.dim == 1) {
-        OpApply<T, 0> op{F, nullptr, (C2<T>*)out, (const T*)V, beta, omega, 1, nl};
-        return launch_pass<T, 0>(g, B, tw.get(0, f64), op, none, s);
+        OpApply<T, 0> op{F, nullptr, O, (const T*)V, beta, omega, 1, nl};
+        return launch_pass<T, 0>(g, B, tw.get(0, f64), op, Partials{nullptr, 0, 0, 0}, s);
     }
-    if (plane_preferred(g, f64, B)) {
-        // whole xy-planes in LDS: all of H f in 2-D; in 3-D the xy-part into tmp, then the z pass
-        if (g.dim == 2) return op_apply_plane(g, f64, B, tw, f, V, out, beta, omega, nl, s);
-        if ((e = op_apply_plane(g, f64, B, tw, f, V, tmp, beta, omega, nl, s)) != hipSuccess) return e;
-        OpApply<T, 2> oz{F, (const C2<T>*)tmp, (C2<T>*)out, nullptr, beta, omega, 0, nl};
-        return launch_pass<T, 2>(g, B, tw.get(2, f64), oz, none, s);
+    const bool plane = plane_preferred(g, f64, B);
+    if (plane && g.dim == 2) return op_apply_plane(g, f64, B, tw, f, V, out, beta, omega, nl, s);  // all of H f
+    int C[3] = {0, 0, 0};
+    for (int a = 0; a < g.dim; ++a) C[a] = pass_lines_per_block(g, a, (int)sizeof(C2<T>), B, false);
+    const int part = apply_part(g, (int)sizeof(C2<T>), B);
+    for (int b = 0; b < B; b += part) {
+        const int64_t off = (int64_t)b * g.N;
+        const hipError_t e = apply_part_t<T>(g, std::min(part, B - b), tw, F + off, (const T*)V, O + off, (C2<T>*)tmp,
+                                             beta, omega, nl, plane, C, s);
+        if (e != hipSuccess) return e;
     }
-    // x-pass (with the pointwise part) into tmp, then the y (and z) passes accumulate.
-    OpApply<T, 0> ox{F, nullptr, (C2<T>*)tmp, (const T*)V, beta, omega, 1, nl};
-    if ((e = launch_pass<T, 0>(g, B, tw.get(0, f64), ox, none, s)) != hipSuccess) return e;
-    if (g.dim == 2) {
-        OpApply<T, 1> oy{F, (const C2<T>*)tmp, (C2<T>*)out, nullptr, beta, omega, 0, nl};
-        return launch_pass<T, 1>(g, B, tw.get(1, f64), oy, none, s);
-    }
-    OpApply<T, 1> oy{F, (const C2<T>*)tmp, (C2<T>*)tmp, nullptr, beta, omega, 0, nl};
-    if ((e = launch_pass<T, 1>(g, B, tw.get(1, f64), oy, none, s)) != hipSuccess) return e;
-    OpApply<T, 2> oz{F, (const C2<T>*)tmp, (C2<T>*)out, nullptr, beta, omega, 0, nl};
-    return launch_pass<T, 2>(g, B, tw.get(2, f64), oz, none, s);
+    return hipSuccess;
 }
 
 // out = R f with R = -L_z (rotation symbol with omega = 1, no kinetic, no potential); dim >= 2.
