@@ -52,7 +52,7 @@ __global__ __launch_bounds__(256) void k_be_resmax(const C2<T>* hphi, const C2<T
         const C2<T> r = sub(hphi[i], scl(phi[i], lam));
         m[0] = fmax(m[0], (double)abs2(r));
     }
-    block_reduce<1>(m, red, out, 1u);
+    block_reduce<1, 1u>(m, red, out);
     if (threadIdx.x == 0) parts[blockIdx.x] = out[0];
 }
 
@@ -62,7 +62,7 @@ __global__ void k_be_scalars(const double* parts, int nb, double* sc, double inv
     __shared__ double out[1];
     double m[1] = {0.0};
     for (int b = threadIdx.x; b < nb; b += blockDim.x) m[0] = fmax(m[0], parts[b]);
-    block_reduce<1>(m, red, out, 1u);
+    block_reduce<1, 1u>(m, red, out);
     if (threadIdx.x == 0) {
         sc[4] = sqrt(out[0]);
         sc[5] = sc[0] / sc[1];

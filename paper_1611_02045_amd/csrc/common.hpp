@@ -110,54 +110,146 @@ enum : int { ST_OK = 0, ST_NOT_CONVERGED = 1, ST_LINESEARCH = -5, ST_NONFINITE =
 
 // ------------------------------------------------------------------------------------------------
 // Deterministic block reduction of K doubles.  Entry k is summed, or max-reduced when bit k of
-// `maxmask` is set.  Inside a full wave the K entries are reduced by a transposing butterfly: at
+// MASK is set.  Inside a full wave the K entries are reduced by a transposing butterfly: at
 // each of the first log2(K') exchanges (K' = K rounded up to a power of two) a lane keeps half of
-// its entries and trades the other half with its partner; after log2(64 / K') plain xor steps
-// lane l holds entry l / (64 / K') summed over the wave, for K' - 1 + log2(64 / K') exchanges in
-// total instead of 6 K.  Blocks whose size is not a multiple of 64 take a masked xor tree per entry (lanes beyond
-// the block's last thread contribute the identity).  The waves are then combined in a fixed order.
-// `red` is LDS scratch of at least (blockDim/64 + 1) * K doubles; `out` is an LDS array of K
-// doubles that holds the totals for every thread on return; v is clobbered.  Must be called by
-// every thread of the block, in uniform control flow.
+// its entries and trades the other half with its partner; after log2(64 / K') plain steps
+// lane l holds entry l / (64 / K') reduced over the wave, for K' - 1 + log2(64 / K') exchanges in
+// total instead of 6 K.  Partners are 32 and 16 lanes apart in the first two exchanges, where the
+// half-wave and row swaps trade two registers in one instruction and leave both addends in place (no
+// selects), and within a row of 16 lanes (data-parallel primitives) after that: through LDS
+// (ds_bpermute) an exchange of one double costs four selects, two LDS trips and their wait, and the
+// reduction of 16 sums took 1.1 us of each small pass.  Blocks whose size is not a multiple of 64 take a masked xor
+// tree per entry (lanes beyond the block's last thread contribute the identity).  The waves are then
+// combined in a fixed order by the first K threads, which hand each total to `sink(k, total)`.
+// `red` is LDS scratch of at least (blockDim/64 + 1) * K doubles; v is clobbered.  Must be called by
+// every thread of the block, in uniform control flow; the sink's writes need a barrier before another
+// thread reads them.
 // ------------------------------------------------------------------------------------------------
-// One exchange of the transposing butterfly (HALF entries traded with the lane at distance OFF),
-// then the next; template recursion keeps every register index a compile-time constant.
-template <int HALF, int OFF, int KP>
-__device__ __forceinline__ void butterfly_round(double (&u)[KP], int lane, int& base, unsigned maxmask) {
-    if constexpr (HALF >= 1) {
-        const bool up = (lane & OFF) != 0;
-#pragma unroll
-        for (int j = 0; j < HALF; ++j) {
-            const double keep = up ? u[j + HALF] : u[j];
-            const double send = up ? u[j] : u[j + HALF];
-            const double recv = __shfl_xor(send, OFF, 64);
-            const bool mx = (maxmask >> (base + (up ? HALF : 0) + j)) & 1u;
-            u[j] = mx ? fmax(keep, recv) : keep + recv;
-        }
-        base += up ? HALF : 0;
-        butterfly_round<HALF / 2, OFF / 2, KP>(u, lane, base, maxmask);
+struct U2 {
+    unsigned x, y;
+};
+__device__ __forceinline__ U2 bits_of(double v) { return __builtin_bit_cast(U2, v); }
+__device__ __forceinline__ double of_bits(unsigned lo, unsigned hi) { return __builtin_bit_cast(double, U2{lo, hi}); }
+
+// Lanes of the upper half (OFF = 32: the wave's, 16: each row pair's) of `a` trade places with those of
+// the lower half of `b`: afterwards a and b hold, in the lower half's lanes, a of both halves, and in the
+// upper half's lanes, b of both.
+template <int OFF>
+__device__ __forceinline__ void swap_halves(double& a, double& b) {
+    static_assert(OFF == 32 || OFF == 16, "half-wave or row swap");
+    const U2 p = bits_of(a), q = bits_of(b);
+    if constexpr (OFF == 32) {
+        const auto lo = __builtin_amdgcn_permlane32_swap(p.x, q.x, false, false);
+        const auto hi = __builtin_amdgcn_permlane32_swap(p.y, q.y, false, false);
+        a = of_bits(lo[0], hi[0]);
+        b = of_bits(lo[1], hi[1]);
+    } else {
+        const auto lo = __builtin_amdgcn_permlane16_swap(p.x, q.x, false, false);
+        const auto hi = __builtin_amdgcn_permlane16_swap(p.y, q.y, false, false);
+        a = of_bits(lo[0], hi[0]);
+        b = of_bits(lo[1], hi[1]);
     }
 }
 
-template <int K>
-__device__ __forceinline__ void block_reduce(double (&v)[K], double* red, double* out, unsigned maxmask) {
-    static_assert(K >= 1 && K <= 64, "block_reduce handles 1..64 entries");
+// The partner's value within a row of 16 lanes: lane xor 8 (rotation by 8), the mirror image within
+// eight lanes (its bit 2 differs), lane xor 2, lane xor 1.
+template <int OFF>
+__device__ __forceinline__ double row_partner(double v) {
+    static_assert(OFF == 8 || OFF == 4 || OFF == 2 || OFF == 1, "partner within a row");
+    constexpr int ctrl = OFF == 8 ? 0x128 : OFF == 4 ? 0x141 : OFF == 2 ? 0x4E : 0xB1;
+    const U2 p = bits_of(v);
+    return of_bits((unsigned)__builtin_amdgcn_mov_dpp((int)p.x, ctrl, 0xF, 0xF, true),
+                   (unsigned)__builtin_amdgcn_mov_dpp((int)p.y, ctrl, 0xF, 0xF, true));
+}
+
+// v and its partner's value at distance OFF, in an order that is the same in both lanes where the
+// hardware swap gives it (OFF >= 16).
+template <int OFF>
+__device__ __forceinline__ void partner_pair(double& a, double& b) {
+    if constexpr (OFF >= 16) {
+        b = a;
+        swap_halves<OFF>(a, b);
+    } else {
+        b = row_partner<OFF>(a);
+    }
+}
+
+// Whether any / all of the entries congruent to j modulo HALF are max-reduced (bits of mask below K).
+__host__ __device__ constexpr bool any_max(unsigned mask, int j, int half, int K) {
+    for (int e = j; e < K; e += half)
+        if ((mask >> e) & 1u) return true;
+    return false;
+}
+__host__ __device__ constexpr bool all_max(unsigned mask, int j, int half, int K) {
+    for (int e = j; e < K; e += half)
+        if (!((mask >> e) & 1u)) return false;
+    return true;
+}
+
+// One exchange of the transposing butterfly (HALF entries traded with the lane at distance OFF),
+// then the next; template recursion keeps every register index a compile-time constant.  Entry
+// base + j is in u[j]; only an index that some lane holds a max entry at pays for the choice.
+template <int HALF, int OFF, int K, unsigned MASK, int KP, int J = 0>
+__device__ __forceinline__ void butterfly_round(double (&u)[KP], int lane, int& base) {
+    if constexpr (HALF >= 1) {
+        const bool up = (lane & OFF) != 0;
+        double a, b;
+        if constexpr (OFF >= 16) {
+            a = u[J];
+            b = u[J + HALF];
+            swap_halves<OFF>(a, b);
+        } else {
+            a = up ? u[J + HALF] : u[J];
+            b = row_partner<OFF>(up ? u[J] : u[J + HALF]);
+        }
+        if constexpr (!any_max(MASK, J, HALF, K)) {
+            u[J] = a + b;
+        } else if constexpr (all_max(MASK, J, HALF, K)) {
+            u[J] = fmax(a, b);
+        } else {
+            const bool mx = (MASK >> (base + (up ? HALF : 0) + J)) & 1u;
+            u[J] = mx ? fmax(a, b) : a + b;
+        }
+        if constexpr (J + 1 < HALF) {
+            butterfly_round<HALF, OFF, K, MASK, KP, J + 1>(u, lane, base);
+        } else {
+            base += up ? HALF : 0;
+            butterfly_round<HALF / 2, OFF / 2, K, MASK, KP>(u, lane, base);
+        }
+    }
+}
+
+// The plain steps at distances OFF, OFF / 2, ..., 1.
+template <int OFF, int K, unsigned MASK>
+__device__ __forceinline__ void plain_steps(double& u, bool mx) {
+    if constexpr (OFF >= 1) {
+        double a = u, b;
+        partner_pair<OFF>(a, b);
+        if constexpr (!any_max(MASK, 0, 1, K)) {
+            u = a + b;
+        } else if constexpr (all_max(MASK, 0, 1, K)) {
+            u = fmax(a, b);
+        } else {
+            u = mx ? fmax(a, b) : a + b;
+        }
+        plain_steps<OFF / 2, K, MASK>(u, mx);
+    }
+}
+
+template <int K, unsigned MASK, class Sink>
+__device__ __forceinline__ void block_reduce_to(double (&v)[K], double* red, Sink sink) {
+    static_assert(K >= 1 && K <= 32, "block_reduce handles 1..32 entries");
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int nw = (blockDim.x + 63) >> 6;
     if ((blockDim.x & 63u) == 0) {
-        constexpr int KP = K <= 1 ? 1 : K <= 2 ? 2 : K <= 4 ? 4 : K <= 8 ? 8 : K <= 16 ? 16 : K <= 32 ? 32 : 64;
+        constexpr int KP = K <= 1 ? 1 : K <= 2 ? 2 : K <= 4 ? 4 : K <= 8 ? 8 : K <= 16 ? 16 : 32;
         double u[KP];
 #pragma unroll
         for (int k = 0; k < KP; ++k) u[k] = k < K ? v[k] : 0.0;  // padding entries are sums of zeros
         int base = 0;  // first entry index still held by this lane
-        butterfly_round<KP / 2, 32>(u, lane, base, maxmask);
-        const bool mx = (maxmask >> base) & 1u;
-#pragma unroll
-        for (int off = 32 / KP; off >= 1; off >>= 1) {
-            const double o = __shfl_xor(u[0], off, 64);
-            u[0] = mx ? fmax(u[0], o) : u[0] + o;
-        }
+        butterfly_round<KP / 2, 32, K, MASK>(u, lane, base);
+        plain_steps<32 / KP, K, MASK>(u[0], (MASK >> base) & 1u);
         __syncthreads();
         if ((lane & (64 / KP - 1)) == 0 && base < K) red[wave * K + base] = u[0];
     } else {
@@ -165,7 +257,8 @@ __device__ __forceinline__ void block_reduce(double (&v)[K], double* red, double
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             double s = v[k];
-            const bool mx = (maxmask >> k) & 1u;
+            constexpr unsigned mask = MASK;
+            const bool mx = (mask >> k) & 1u;
 #pragma unroll
             for (int off = 32; off > 0; off >>= 1) {
                 double o = __shfl_xor(s, off, 64);
@@ -182,14 +275,20 @@ __device__ __forceinline__ void block_reduce(double (&v)[K], double* red, double
     }
     __syncthreads();
     for (int k = threadIdx.x; k < K; k += blockDim.x) {
-        const bool mx = (maxmask >> k) & 1u;
+        const bool mx = (MASK >> k) & 1u;
         double s = red[k];
         for (int w = 1; w < nw; ++w) {
             const double o = red[w * K + k];
             s = mx ? fmax(s, o) : s + o;
         }
-        out[k] = s;
+        sink(k, s);
     }
+}
+
+// block_reduce_to with the totals in `out` (LDS, K doubles), visible to every thread on return.
+template <int K, unsigned MASK = 0u>
+__device__ __forceinline__ void block_reduce(double (&v)[K], double* red, double* out) {
+    block_reduce_to<K, MASK>(v, red, [out](int k, double s) { out[k] = s; });
     __syncthreads();
 }
 

@@ -30,7 +30,7 @@ __global__ __launch_bounds__(256) void k_dots(DotReq<T> q, int nq, int64_t N, do
             }
         }
     }
-    block_reduce<4>(acc, red, out, 0u);
+    block_reduce<4>(acc, red, out);
     if (threadIdx.x < 4) parts[blockIdx.x * 4 + threadIdx.x] = out[threadIdx.x];
 }
 
@@ -41,7 +41,7 @@ static __global__ void k_dots_final(const double* parts, int nb, double scale, d
     double acc[4] = {0.0, 0.0, 0.0, 0.0};
     for (int b = threadIdx.x; b < nb; b += blockDim.x)
         for (int k = 0; k < 4; ++k) acc[k] += parts[b * 4 + k];
-    block_reduce<4>(acc, red, out, 0u);
+    block_reduce<4>(acc, red, out);
     if (threadIdx.x < 4) dst[threadIdx.x] = scale * out[threadIdx.x];
 }
 

@@ -418,7 +418,7 @@ __global__ void k_energy_collect(const double* p0, int n0, const double* p1, int
             for (int k = 0; k < 4; ++k) v[k] += ps[q][(size_t)blk * 4 + k];
     }
     __shared__ double T4[4];
-    block_reduce<4>(v, red, T4, 0u);
+    block_reduce<4>(v, red, T4);
     if (threadIdx.x == 0) {
         dst[0] = cell * T4[0];               // <phi, T phi>
         dst[1] = cell * T4[2];               // <phi, V phi>
@@ -635,7 +635,7 @@ __global__ void k_min_diag(const C2<T>* phi, const T* V, const double* alpha, do
         m[0] = fmin(m[0], a + (double)V[i] + beta * (double)abs2(phi[i]));
     m[0] = -m[0];
     __shared__ double o1[1];
-    block_reduce<1>(m, red, o1, 1u);
+    block_reduce<1, 1u>(m, red, o1);
     if (threadIdx.x == 0) parts[blockIdx.x] = -o1[0];
 }
 

@@ -163,20 +163,19 @@ struct Partials {
 
 // Sum K partials of instance b over its nb blocks with all threads of the (last) block, in a
 // fixed order.  `red` is block_reduce scratch; `out` (LDS, K doubles) receives the totals.
-template <int K>
-__device__ __forceinline__ void reduce_partials(const double* parts, int nb, double* red, double* out,
-                                                unsigned maxmask) {
+template <int K, unsigned MASK>
+__device__ __forceinline__ void reduce_partials(const double* parts, int nb, double* red, double* out) {
     double acc[K];
 #pragma unroll
-    for (int k = 0; k < K; ++k) acc[k] = ((maxmask >> k) & 1u) ? -1e300 : 0.0;
+    for (int k = 0; k < K; ++k) acc[k] = ((MASK >> k) & 1u) ? -1e300 : 0.0;
     for (int blk = threadIdx.x; blk < nb; blk += blockDim.x) {
 #pragma unroll
         for (int k = 0; k < K; ++k) {
             const double p = parts[(size_t)blk * K + k];
-            acc[k] = ((maxmask >> k) & 1u) ? fmax(acc[k], p) : acc[k] + p;
+            acc[k] = ((MASK >> k) & 1u) ? fmax(acc[k], p) : acc[k] + p;
         }
     }
-    block_reduce<K>(acc, red, out, maxmask);
+    block_reduce<K, MASK>(acc, red, out);
 }
 
 // Loads a solver pass issues before everything else (state, partial rows of its producers).
@@ -324,11 +323,8 @@ void pass_kernel(Geo g, int C, const C2<T>* __restrict__ twg, Op op, Partials pr
     op.store(g, lc, st, v, acc);
 
     if constexpr (Op::K > 0) {
-        const int nw = (blockDim.x + 63) >> 6;
-        double* outK = red + (size_t)nw * Op::K;
-        block_reduce<Op::K>(acc, red, outK, Op::MAXMASK);
         double* P = pr.parts + ((size_t)lc.b * pr.row_stride() + pr.off + blk_in_inst) * Op::K;
-        for (int k = threadIdx.x; k < Op::K; k += blockDim.x) P[k] = outK[k];
+        block_reduce_to<Op::K, Op::MAXMASK>(acc, red, [P](int k, double s) { P[k] = s; });
     }
 }
 

@@ -45,23 +45,21 @@ __global__ __launch_bounds__(256) void k_resid_diag(IterFields<T> f, const Scal*
         res_sums<T>(acc, r);
         cg_sums<T>(acc, r, prv, f.rp[i], f.pp[i], ph);
     }
-    __shared__ double totals[A_K];
-    block_reduce<A_K>(acc, red, totals, A_MAXMASK);
     double* P = pr.parts + ((size_t)b * pr.row_stride() + pr.off + blk) * A_K;
-    for (int k = threadIdx.x; k < A_K; k += blockDim.x) P[k] = totals[k];
+    block_reduce_to<A_K, A_MAXMASK>(acc, red, [P](int k, double t) { P[k] = t; });
 }
 
 // ---------------------------------------------------------------------------------------------
 // Collapse the per-block partial rows of each instance into one row (one workgroup per instance,
 // fixed order), so that the consuming pass's workgroups reduce a single row.
 // ---------------------------------------------------------------------------------------------
-template <int K>
-__global__ __launch_bounds__(256) void k_collapse(const double* parts, int nb, int stride, double* out, unsigned mask,
+template <int K, unsigned MASK>
+__global__ __launch_bounds__(256) void k_collapse(const double* parts, int nb, int stride, double* out,
                                                  int b0, const int* imap) {
     __shared__ double red[(256 / 64 + 1) * K];
     __shared__ double tot[K];
     const int b = imap ? imap[blockIdx.x] : b0 + (int)blockIdx.x;
-    reduce_partials<K>(parts + (size_t)b * stride * K, nb, red, tot, mask);
+    reduce_partials<K, MASK>(parts + (size_t)b * stride * K, nb, red, tot);
     for (int k = threadIdx.x; k < K; k += blockDim.x) out[(size_t)b * K + k] = tot[k];
 }
 
@@ -85,15 +83,15 @@ hipError_t enqueue_iteration(const IterCtx<T>& c, hipStream_t s) {
         return Partials{c.parts + (size_t)r * c.region_doubles, nb, nb, 0};
     };
     // the view a consumer absorbs: the region itself, or its one-row collapse for many rows
-    auto consumable = [&](const Partials& p, int rc, int K, unsigned mask) -> Partials {
+    auto consumable = [&](const Partials& p, int rc, int K) -> Partials {
         if (p.nb <= kAbsorbRows) return p;
         const Partials q{c.parts + (size_t)rc * c.region_doubles, 1, 1, 0};
         if (K == A_K)
-            hipLaunchKernelGGL(k_collapse<A_K>, dim3((unsigned)Bl), dim3(256), 0, s, p.parts, p.nb, p.row_stride(),
-                               q.parts, mask, g.b0, g.imap);
+            hipLaunchKernelGGL((k_collapse<A_K, A_MAXMASK>), dim3((unsigned)Bl), dim3(256), 0, s, p.parts, p.nb, p.row_stride(),
+                               q.parts, g.b0, g.imap);
         else
-            hipLaunchKernelGGL(k_collapse<B_K>, dim3((unsigned)Bl), dim3(256), 0, s, p.parts, p.nb, p.row_stride(),
-                               q.parts, mask, g.b0, g.imap);
+            hipLaunchKernelGGL((k_collapse<B_K, B_MAXMASK>), dim3((unsigned)Bl), dim3(256), 0, s, p.parts, p.nb, p.row_stride(),
+                               q.parts, g.b0, g.imap);
         return q;
     };
     const Partials none{nullptr, 0, 0, 0};
@@ -129,7 +127,7 @@ hipError_t enqueue_iteration(const IterCtx<T>& c, hipStream_t s) {
         launch_timed(tick("step_resid_diag", 21), k_resid_diag<T>, dim3((unsigned)(nbpi * Bl)), dim3(256), 0, s, f,
                      S_dir, S_step, g.N, nbpi, pre, sb, pr, g.b0, g.imap);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        pres = consumable(pr, R_A1C, A_K, A_MAXMASK);
+        pres = consumable(pr, R_A1C, A_K);
         pdir = pres;
         dir_in = S_step;
     } else if (g.dim == 1) {
@@ -138,7 +136,7 @@ hipError_t enqueue_iteration(const IterCtx<T>& c, hipStream_t s) {
         if ((e = launch_pass<T, 0>(g, c.B, c.tw->get(0, f64), op, pa, s,
                 tick("step_resid_precond_x", 21))) != hipSuccess)
             return e;
-        pres = consumable(pa, R_A1C, A_K, A_MAXMASK);
+        pres = consumable(pa, R_A1C, A_K);
         pdir = pres;
         dir_in = S_step;
     } else {
@@ -147,7 +145,7 @@ hipError_t enqueue_iteration(const IterCtx<T>& c, hipStream_t s) {
         if ((e = launch_pass<T, 0>(g, c.B, c.tw->get(0, f64), op, pa1r, s,
                 tick("step_resid_fwd_x", 17))) != hipSuccess)
             return e;
-        const Partials pa1 = consumable(pa1r, R_A1C, A_K, A_MAXMASK);
+        const Partials pa1 = consumable(pa1r, R_A1C, A_K);
         if (g.dim == 2) {
             OpPMid<T, 1, true, true, true> y{f.w, S_step, S_res, pa1};
             if ((e = launch_pass<T, 1>(g, c.B, c.tw->get(1, f64), y, none, s,
@@ -172,7 +170,7 @@ hipError_t enqueue_iteration(const IterCtx<T>& c, hipStream_t s) {
         if ((e = launch_pass<T, 0>(g, c.B, c.tw->get(0, f64), op3, pa3, s,
                 tick("precond_inv_x", 13))) != hipSuccess)
             return e;
-        pdir = consumable(pa3, R_A3C, A_K, A_MAXMASK);
+        pdir = consumable(pa3, R_A3C, A_K);
         dir_in = S_res;
     }
     // ---- phase B ----
@@ -202,7 +200,7 @@ hipError_t enqueue_iteration(const IterCtx<T>& c, hipStream_t s) {
                 tick("Lp_z_linesearch", 8))) != hipSuccess)
             return e;
     }
-    (void)consumable(pbAll, R_BC, B_K, B_MAXMASK);
+    (void)consumable(pbAll, R_BC, B_K);
     return hipGetLastError();
 }
 

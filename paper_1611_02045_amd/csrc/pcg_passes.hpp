@@ -450,12 +450,12 @@ struct StateChunk {
 // groups of each wave by two exchanges and the waves through LDS, in a fixed order.  Blocks that
 // are not whole waves fetch nothing early and reduce row by row.  Rows may be stale (a region
 // whose sums are not pending), never out of bounds.
-template <int K, int NV>
+template <int K, int NV, unsigned mask>
 struct RowFetch {
     static_assert(K >= 1 && K <= 16, "up to 16 sums per row");
     double v[NV];
     __device__ __forceinline__ static bool fast() { return (blockDim.x & 63u) == 0; }
-    __device__ __forceinline__ void issue(const Partials& P, int b, unsigned mask) {
+    __device__ __forceinline__ void issue(const Partials& P, int b) {
         if (!fast() || !P.parts || P.nb <= 0) return;
         const int k = threadIdx.x & 15, grp = threadIdx.x >> 4, G = blockDim.x >> 4;
         const double id = ((mask >> k) & 1u) ? -1e300 : 0.0;
@@ -468,7 +468,7 @@ struct RowFetch {
             v[j] = (k < K && r < P.nb) ? x : id;
         }
     }
-    __device__ __forceinline__ void reduce(const Partials& P, int b, unsigned mask, double* red, double* tot) const {
+    __device__ __forceinline__ void reduce(const Partials& P, int b, double* red, double* tot) const {
         if (!P.parts || P.nb <= 0) {
             for (int k = threadIdx.x; k < K; k += blockDim.x) tot[k] = ((mask >> k) & 1u) ? -1e300 : 0.0;
             __syncthreads();
@@ -476,7 +476,7 @@ struct RowFetch {
         }
         const double* rows = P.parts + (size_t)b * P.row_stride() * K;
         if (!fast()) {
-            reduce_partials<K>(rows, P.nb, red, tot, mask);
+            reduce_partials<K, mask>(rows, P.nb, red, tot);
             return;
         }
         const int k = threadIdx.x & 15, grp = threadIdx.x >> 4, G = blockDim.x >> 4;
@@ -486,9 +486,10 @@ struct RowFetch {
         for (int j = 1; j < NV; ++j) a = mx ? fmax(a, v[j]) : a + v[j];
         if (k < K)
             for (int r = grp + NV * G; r < P.nb; r += G) a = mx ? fmax(a, rows[(size_t)r * K + k]) : a + rows[(size_t)r * K + k];
-        double o = __shfl_xor(a, 16, 64);
+        double o;
+        partner_pair<16>(a, o);
         a = mx ? fmax(a, o) : a + o;
-        o = __shfl_xor(a, 32, 64);
+        partner_pair<32>(a, o);
         a = mx ? fmax(a, o) : a + o;
         const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
         if (lane < 16) red[wave * 16 + lane] = a;
@@ -507,10 +508,10 @@ struct IntakeState {
     StateChunk st;
 };
 // What a pass that absorbs a region of K-sum rows fetches early (NV rows per thread in registers).
-template <int K, int NV>
+template <int K, int NV, unsigned MASK>
 struct IntakeAbsorb {
     StateChunk st;
-    RowFetch<K, NV> rows;
+    RowFetch<K, NV, MASK> rows;
 };
 
 // Copy the fetched state into LDS and barrier.
@@ -536,11 +537,12 @@ __device__ __forceinline__ void finish(Scal* s, const double* tot, int blk, F fn
 
 // Start of an absorbing pass: the fetched state into LDS, the fetched rows reduced into `tot`
 // (LDS, K doubles; the reduction's barriers also publish the state), then `fn` on thread 0.
-template <int K, int NV, class F>
-__device__ __forceinline__ void absorb_finish(const Scal* in, int b, int blk, Scal* s, const IntakeAbsorb<K, NV>& it,
-                                              const Partials& P, unsigned mask, double* red, double* tot, F fn) {
+template <int K, int NV, unsigned MASK, class F>
+__device__ __forceinline__ void absorb_finish(const Scal* in, int b, int blk, Scal* s,
+                                              const IntakeAbsorb<K, NV, MASK>& it, const Partials& P, double* red,
+                                              double* tot, F fn) {
     it.st.store(in, b, s);
-    it.rows.reduce(P, b, mask, red, tot);
+    it.rows.reduce(P, b, red, tot);
     finish<K>(s, tot, blk, fn);
 }
 
@@ -581,16 +583,16 @@ __device__ __forceinline__ int full_scan_wave(const Scal& S, const double* t) {
 // The step at the start of phase A, from the direction sums of every pass of phase B (one region,
 // B sums), when they are pending: the line search and the predicted scalars of the new iterate.
 constexpr int kStepRowsPerThread = 16;   // 256 rows with 256-thread blocks
-using IntakeStep = IntakeAbsorb<B_K, kStepRowsPerThread>;
+using IntakeStep = IntakeAbsorb<B_K, kStepRowsPerThread, B_MAXMASK>;
 __device__ __forceinline__ void intake_step(const Scal* in, const Partials& pb, int b, IntakeStep& it) {
     it.st.issue(in, b);
-    it.rows.issue(pb, b, B_MAXMASK);
+    it.rows.issue(pb, b);
 }
 __device__ __forceinline__ void begin_step(const Scal* in, Scal* out, const Partials& pb, int b, int blk, double* red,
                                            Scal* s, const IntakeStep& it) {
     __shared__ double tot[B_K];
     it.st.store(in, b, s);
-    it.rows.reduce(pb, b, B_MAXMASK, red, tot);  // ends with a barrier: s and tot are visible
+    it.rows.reduce(pb, b, red, tot);  // ends with a barrier: s and tot are visible
     int kb = -1;
     if (s->line_search == 2 && !s->done && s->b_phase && blockDim.x >= 64 && threadIdx.x < 64)
         kb = full_scan_wave(*s, tot);  // the whole first wave takes this branch (s is uniform)
@@ -606,7 +608,7 @@ __device__ __forceinline__ void begin_step(const Scal* in, Scal* out, const Part
 // Passes that absorb the phase-A sums (A_K per row, one region of at most 128 rows per thread
 // group's registers).
 constexpr int kARowsPerThread = 8;
-using IntakeA = IntakeAbsorb<A_K, kARowsPerThread>;
+using IntakeA = IntakeAbsorb<A_K, kARowsPerThread, A_MAXMASK>;
 
 // ---------------------------------------------------------------------------------------------
 // Phase A, first pass (x): [step from the direction sums], the pending retraction applied to
@@ -727,7 +729,7 @@ struct OpPMid {
     __device__ void intake(int b, int blk, Intake& it) const {
         it.st.issue(Sin, b);
         if constexpr (ABS)
-            if (blk == 0) it.rows.issue(pa1, b, A_MAXMASK);
+            if (blk == 0) it.rows.issue(pa1, b);
     }
     struct State {
         C2<T> w[8];
@@ -741,7 +743,7 @@ struct OpPMid {
         if constexpr (ABS) {
             if (blk == 0) {
                 __shared__ double tot[A_K];
-                absorb_finish(Sin, b, blk, s, it, pa1, A_MAXMASK, red, tot, [](Scal& S, const double* t) {
+                absorb_finish(Sin, b, blk, s, it, pa1, red, tot, [](Scal& S, const double* t) {
                     if (!S.done) fin_residual(S, t);
                 });
                 state_publish(Sout, b, blk, s);
@@ -858,7 +860,7 @@ struct OpLp {
     using Intake = std::conditional_t<FIRST, IntakeA, IntakeState>;
     __device__ void intake(int b, int, Intake& it) const {
         it.st.issue(Sin, b);
-        if constexpr (FIRST) it.rows.issue(pdir, b, A_MAXMASK);
+        if constexpr (FIRST) it.rows.issue(pdir, b);
     }
     struct State {
         C2<T> ph[8];
@@ -892,7 +894,7 @@ struct OpLp {
             // on the one-pass paths the convergence test reads the same region as the direction
             __shared__ double tot[A_K];
             it.st.store(Sin, b, s);
-            it.rows.reduce(pdir, b, A_MAXMASK, red, tot);
+            it.rows.reduce(pdir, b, red, tot);
             auto direction = [](Scal& S, const double* t) {
                 if (!S.done) {
                     fin_direction(S, t);

@@ -47,7 +47,7 @@ __global__ __launch_bounds__(256) void k_norm_partial(const C2<T>* phi, int64_t 
     double v[1] = {0.0};
     for (int64_t j = lo + threadIdx.x; j < hi; j += blockDim.x) v[0] += (double)abs2(phi[(int64_t)b * N + j]);
     __shared__ double o1[1];
-    block_reduce<1>(v, red, o1, 0u);
+    block_reduce<1>(v, red, o1);
     if (threadIdx.x == 0) parts[blockIdx.x] = o1[0];
 }
 
@@ -61,7 +61,7 @@ __global__ __launch_bounds__(256) void k_norm_apply(C2<T>* phi, int64_t N, int n
     double v[1] = {0.0};
     for (int k = threadIdx.x; k < nbpi; k += blockDim.x) v[0] += parts[(size_t)b * nbpi + k];
     __shared__ double o1[1];
-    block_reduce<1>(v, red, o1, 0u);
+    block_reduce<1>(v, red, o1);
     if (threadIdx.x == 0) inv = 1.0 / sqrt(S[b].cell * o1[0]);
     __syncthreads();
     const int64_t chunk = (N + nbpi - 1) / nbpi, lo = (int64_t)blk * chunk, hi = min(N, lo + chunk);
@@ -105,7 +105,7 @@ __global__ __launch_bounds__(256) void k_verify_dot(const C2<T>* phi, const C2<T
         v[1] += (double)abs2(phi[i]);
     }
     __shared__ double o2[2];
-    block_reduce<2>(v, red, o2, 0u);
+    block_reduce<2>(v, red, o2);
     if (threadIdx.x < 2) parts[blockIdx.x * 2 + threadIdx.x] = o2[threadIdx.x];
 }
 
@@ -120,7 +120,7 @@ __global__ __launch_bounds__(256) void k_verify_res(const C2<T>* phi, const C2<T
         v[1] += dots[2 * k + 1];
     }
     __shared__ double t2[2];
-    block_reduce<2>(v, red, t2, 0u);
+    block_reduce<2>(v, red, t2);
     if (threadIdx.x == 0) {
         lam_s = t2[0] / t2[1];
         if (blockIdx.x == 0) *lam_out = lam_s;
@@ -134,7 +134,7 @@ __global__ __launch_bounds__(256) void k_verify_res(const C2<T>* phi, const C2<T
         m[0] = fmax(m[0], sqrt(rx * rx + ry * ry));
     }
     __shared__ double o1[1];
-    block_reduce<1>(m, red, o1, 1u);
+    block_reduce<1, 1u>(m, red, o1);
     if (threadIdx.x == 0) maxparts[blockIdx.x] = o1[0];
 }
 
