@@ -639,12 +639,11 @@ __global__ void k_min_diag(const C2<T>* phi, const T* V, const double* alpha, do
     if (threadIdx.x == 0) parts[blockIdx.x] = -o1[0];
 }
 
-__global__ void k_min_collect(const double* parts, int n, double* dst) {
-    if (threadIdx.x == 0) {
-        double m = parts[0];
-        for (int i = 1; i < n; ++i) m = fmin(m, parts[i]);
-        *dst = m;
-    }
+__global__ __launch_bounds__(256) void k_min_collect(const double* parts, int n, double* dst) {
+    __shared__ double red[8];
+    double m[1] = {-1e300};
+    for (int i = threadIdx.x; i < n; i += blockDim.x) m[0] = fmax(m[0], -parts[i]);
+    block_reduce_to<1, 1u>(m, red, [dst](int, double t) { *dst = -t; });
 }
 
 hipError_t op_min_diag(const Geo& g, bool f64, const void* phi, const void* V, const double* alpha_dev,
@@ -657,7 +656,7 @@ hipError_t op_min_diag(const Geo& g, bool f64, const void* phi, const void* V, c
     else
         hipLaunchKernelGGL(k_min_diag<float>, dim3(blocks), dim3(256), 0, s, (const C2<float>*)phi,
                            (const float*)V, alpha_dev, beta, g.N, parts);
-    hipLaunchKernelGGL(k_min_collect, dim3(1), dim3(64), 0, s, parts, blocks, dst);
+    hipLaunchKernelGGL(k_min_collect, dim3(1), dim3(256), 0, s, parts, blocks, dst);
     return hipGetLastError();
 }
 

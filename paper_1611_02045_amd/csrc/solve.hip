@@ -138,12 +138,12 @@ __global__ __launch_bounds__(256) void k_verify_res(const C2<T>* phi, const C2<T
     if (threadIdx.x == 0) maxparts[blockIdx.x] = o1[0];
 }
 
-__global__ void k_max_collect(const double* parts, int n, double* dst) {
-    if (threadIdx.x == 0) {
-        double m = 0.0;
-        for (int i = 0; i < n; ++i) m = fmax(m, parts[i]);
-        *dst = m;
-    }
+// Maximum of n partials (one workgroup; a single thread's loop over 256 of them took 15 us).
+__global__ __launch_bounds__(256) void k_max_collect(const double* parts, int n, double* dst) {
+    __shared__ double red[8];
+    double m[1] = {0.0};
+    for (int i = threadIdx.x; i < n; i += blockDim.x) m[0] = fmax(m[0], parts[i]);
+    block_reduce_to<1, 1u>(m, red, [dst](int, double t) { *dst = t; });
 }
 
 static unsigned blocks_for(int64_t n) { return (unsigned)((n + 255) / 256); }
@@ -482,7 +482,7 @@ hipError_t verify_field(const Geo& g, const Twiddles& tw, const void* phi, const
     hipLaunchKernelGGL(k_verify_dot<T>, dim3(nb), dim3(256), 0, s, (const C2<T>*)phi, (const C2<T>*)hphi, g.N, parts);
     hipLaunchKernelGGL(k_verify_res<T>, dim3(nb), dim3(256), 0, s, (const C2<T>*)phi, (const C2<T>*)hphi, g.N, parts, nb,
                        parts + 2 * nb, sc + 32);
-    hipLaunchKernelGGL(k_max_collect, dim3(1), dim3(64), 0, s, parts + 2 * nb, nb, sc + 33);
+    hipLaunchKernelGGL(k_max_collect, dim3(1), dim3(256), 0, s, parts + 2 * nb, nb, sc + 33);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if ((e = op_energy(g, f64, tw, phi, V, beta, omega, red, sc + 36, s)) != hipSuccess) return e;
     double h[8];
