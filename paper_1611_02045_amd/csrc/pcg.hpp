@@ -20,8 +20,8 @@ struct IterFields {
     T* V;         // potential
 };
 
-// Partial-sum regions of the reducing passes, and their collapsed counterparts (one row per
-// instance) used when a pass has more workgroups per instance than a consumer should re-reduce.
+// Partial-sum regions of the reducing passes, and their collapsed counterparts (a row per
+// 64 rows) used when a pass has more workgroups per instance than a consumer should re-reduce.
 enum : int {
     R_A1 = 0, R_A3, R_B, R_A1C = R_B + 3, R_A3C, R_BC, R_COUNT  // R_B spans three regions (x, y, z passes)
 };
