@@ -42,8 +42,13 @@ inline void launch_timed(const LaunchEvents* ev, K kern, dim3 grid, dim3 block, 
 
 constexpr size_t kPassLdsBudget = 96 * 1024;
 // Workgroup size cap of the passes: with 256 threads (one wave per SIMD) every kernel may keep up
-// to 256 VGPRs per lane without scratch spills.
+// to 256 VGPRs per lane without scratch spills.  Lines of 5 * 2^k points take up to 320: 320 threads
+// hold whole lines in whole waves (4 lines of 640 points, 8 of 320, ...), where 160 would leave half a
+// wave idle and send every reduction and row intake down the partial-wave path, at half the row
+// segment in strided passes.
 constexpr int kMaxPassThreads = 256;
+constexpr int kMaxPassThreads5 = 320;
+inline int max_pass_threads(const Geo& g, int AX) { return g.f5[AX] ? kMaxPassThreads5 : kMaxPassThreads; }
 
 inline size_t pass_lds_bytes_cb(int cb, int M, int C, int threads, int K, int axis) {
     size_t b = (size_t)cb * ((size_t)M + (size_t)C * line_stride(M, cb, axis, C));
@@ -62,11 +67,11 @@ inline size_t pass_lds_bytes_cb(int cb, int M, int C, int threads, int K, int ax
 int tuned_lines(const Geo& g, int AX, int complex_bytes, int B);
 void record_tuned_lines(const Geo& g, int AX, int complex_bytes, int B, int C);
 
-// Whether C lines per workgroup is a valid tile for a pass along AX (whole lines, at most 256
-// threads, C dividing the lines of a field, strided groups within n_x, LDS within budget).
+// Whether C lines per workgroup is a valid tile for a pass along AX (whole lines, within the thread
+// cap, C dividing the lines of a field, strided groups within n_x, LDS within budget).
 inline bool valid_lines(const Geo& g, int AX, int complex_bytes, int C) {
     const int TPL = g.n[AX] / 8;
-    if (C < 1 || (C & (C - 1)) != 0 || C * TPL > 256) return false;
+    if (C < 1 || (C & (C - 1)) != 0 || C * TPL > max_pass_threads(g, AX)) return false;
     if (lines_per_field(g, AX) % C != 0) return false;
     if (AX != 0 && C > g.n[0]) return false;
     return pass_lds_bytes_cb(complex_bytes, g.n[AX], C, C * TPL, 32, AX) <= kPassLdsBudget;
@@ -84,6 +89,17 @@ inline int pass_lines_rule(const Geo& g, int AX, int complex_bytes, int B) {
     const int64_t lpf = lines_per_field(g, AX);
     const int64_t lines = lpf * (int64_t)B;
     int C;
+    if (g.f5[AX]) {
+        // 320 threads when the launch has 32 such workgroups or more; with 16-byte points only up to one
+        // per CU: their passes leave room for two or three waves per SIMD, where five-wave workgroups
+        // pack worse than two of 160 threads.  Iteration at 640^2 (kernel time, us): one FP64 instance
+        // 120 -> 92, one FP32 100 -> 74; eight FP32 at 320^2 117 -> 94, at 640^2 258 -> 262; eight FP64
+        // (not taken) 465 -> 448 at 640^2, 151 -> 155 at 320^2, its y pass 45 -> 57.
+        C = kMaxPassThreads5 / TPL;
+        const int64_t blocks = lines / C;
+        if (valid_lines(g, AX, complex_bytes, C) && blocks >= 32 && (complex_bytes == 8 || blocks <= device_cus()))
+            return C;
+    }
     if (AX == 0) {
         C = floor_pow2(std::max(1, 256 / TPL));
     } else {
@@ -130,23 +146,26 @@ hipError_t launch_pass(const Geo& g, int B, const void* tw, const Op& op, Partia
     if (pr.stride == 0) pr.stride = nb;
     // reduction scratch sized for the pass's own sums and for absorbing up to 16 sums of its predecessor
     const size_t lds = pass_lds_bytes<T>(g.n[AX], C, threads, Op::K > 16 ? Op::K : 16, AX);
-    if (threads > kMaxPassThreads) return hipErrorInvalidConfiguration;
+    if (threads > max_pass_threads(g, AX)) return hipErrorInvalidConfiguration;
     const int64_t blocks = nb * (int64_t)(g.bl > 0 ? g.bl : B);  // instances [g.b0, g.b0 + g.bl) only
-    // one workgroup per CU or fewer: fetch everything ahead of the scalar logic (see pass_kernel)
-    const bool early = blocks <= device_cus();
+    // one workgroup per CU or fewer: fetch everything ahead of the scalar logic (see pass_kernel);
+    // 320-thread workgroups keep to the late form, whose registers fit the 256 such a block may have
+    const bool wide = threads > kMaxPassThreads;
+    const bool early = blocks <= device_cus() && !wide;
     // lines of 64, 128, 256, 512 and 640 points (the common sizes and the paper's) take the
     // compile-time transform (measured 18% less time per iteration than the run-time one on 256^2,
     // 22-27% on 64^2 and 64^3); other sizes the run-time one
-    constexpr int kMaxT = kMaxPassThreads;
+    constexpr int kMaxT = kMaxPassThreads, kMaxT5 = kMaxPassThreads5;
     const int lg = g.lg[AX];
-    const int ct = g.f5[AX] ? (lg == 7 ? 4 : 0) : (lg == 9 ? 3 : lg == 8 ? 2 : lg == 7 ? 1 : lg == 6 ? 5 : 0);
+    const int ct = g.f5[AX] ? (lg == 7 ? 4 : wide ? 6 : 0) : (lg == 9 ? 3 : lg == 8 ? 2 : lg == 7 ? 1 : lg == 6 ? 5 : 0);
     using K = decltype(&pass_kernel<T, AX, Op, kMaxT, true, 0>);
-    const K variants[12] = {pass_kernel<T, AX, Op, kMaxT, false, 0>,   pass_kernel<T, AX, Op, kMaxT, true, 0>,
-                            pass_kernel<T, AX, Op, kMaxT, false, 7>,   pass_kernel<T, AX, Op, kMaxT, true, 7>,
-                            pass_kernel<T, AX, Op, kMaxT, false, 8>,   pass_kernel<T, AX, Op, kMaxT, true, 8>,
-                            pass_kernel<T, AX, Op, kMaxT, false, 9>,   pass_kernel<T, AX, Op, kMaxT, true, 9>,
-                            pass_kernel<T, AX, Op, kMaxT, false, 107>, pass_kernel<T, AX, Op, kMaxT, true, 107>,
-                            pass_kernel<T, AX, Op, kMaxT, false, 6>,   pass_kernel<T, AX, Op, kMaxT, true, 6>};
+    const K variants[13] = {pass_kernel<T, AX, Op, kMaxT, false, 0>,    pass_kernel<T, AX, Op, kMaxT, true, 0>,
+                            pass_kernel<T, AX, Op, kMaxT, false, 7>,    pass_kernel<T, AX, Op, kMaxT, true, 7>,
+                            pass_kernel<T, AX, Op, kMaxT, false, 8>,    pass_kernel<T, AX, Op, kMaxT, true, 8>,
+                            pass_kernel<T, AX, Op, kMaxT, false, 9>,    pass_kernel<T, AX, Op, kMaxT, true, 9>,
+                            pass_kernel<T, AX, Op, kMaxT5, false, 107>, pass_kernel<T, AX, Op, kMaxT, true, 107>,
+                            pass_kernel<T, AX, Op, kMaxT, false, 6>,    pass_kernel<T, AX, Op, kMaxT, true, 6>,
+                            pass_kernel<T, AX, Op, kMaxT5, false, 0>};
     const K kern = variants[2 * ct + (early ? 1 : 0)];
     static std::once_flag attr_once;  // one attribute call per instantiation set (thread-safe)
     std::call_once(attr_once, [&] {

@@ -312,7 +312,7 @@ static hipError_t tune_axis(const Geo& g, int B, const Twiddles& tw, const C2<T>
     // whole waves where the grid allows it (a partial wave idles lanes)
     int Cmin = 1;
     while (Cmin * TPL < 64 && valid_lines(g, AX, cb, 2 * Cmin)) Cmin *= 2;
-    for (int C = Cmin; C * TPL <= 256 && e == hipSuccess; C *= 2) {
+    for (int C = Cmin; C * TPL <= max_pass_threads(g, AX) && e == hipSuccess; C *= 2) {
         if (!valid_lines(g, AX, cb, C)) continue;
         constexpr int kWarm = 2, kReps = 10;
         for (int r = 0; r < kWarm && e == hipSuccess; ++r) e = launch_pass<T, AX>(g, B, tw.get(AX, sizeof(T) == 8), op, none, s, nullptr, C);
