@@ -100,6 +100,12 @@ hipError_t op_precond(const Geo& g, bool f64, const Twiddles& tw, int kind, cons
                       const void* V, const double* alpha_dev, double beta, const void* r, void* out,
                       void* tmp, hipStream_t s);
 
+// The middle passes of P_Delta (dim >= 2) on a field transformed along x, in place, and the y part of
+// L f added to `out` (the middle pass of a 3-D apply).
+hipError_t op_kinetic_middle(const Geo& g, bool f64, const Twiddles& tw, void* w, const double* alpha_dev,
+                             hipStream_t s);
+hipError_t op_apply_y(const Geo& g, bool f64, const Twiddles& tw, const void* f, void* out, double omega, hipStream_t s);
+
 // Minimum over the grid of alpha + V + beta |phi|^2 into *dst (device).
 hipError_t op_min_diag(const Geo& g, bool f64, const void* phi, const void* V, const double* alpha_dev,
                        double beta, Reduce& red, double* dst, hipStream_t s);

@@ -57,68 +57,6 @@ __global__ void k_zero_c(C2<T>* a, int64_t N) {
     if (i < N) a[i] = mk((T)0, (T)0);
 }
 
-// Device state of a preconditioned linear CG (every scalar stays on the device; the host polls
-// `done`).  lam, beta, cell, nphi2 are parameters of the operator of the solver using it.
-struct CgS {
-    double lam, beta, cell, nphi2;  // chemical potential, nonlinearity, h^d, ||phi||^2
-    double rz, pq, rr, rr0, a, b;
-    double tol2;
-    int64_t it, max_it;
-    int32_t done, status;
-};
-
-static __global__ void k_cg_alpha(CgS* S, const double* pq) {
-    if (threadIdx.x != 0 || S->done) return;
-    S->pq = pq[0];
-    if (!(S->pq > 0.0)) {
-        S->status = -1;  // the operator is not positive definite
-        S->done = 1;
-        return;
-    }
-    S->a = S->rz / S->pq;
-}
-
-template <typename T>
-__global__ void k_cg_update(C2<T>* x, C2<T>* r, const C2<T>* p, const C2<T>* q, const CgS* S, int64_t N) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N || S->done) return;
-    const T a = (T)S->a;
-    x[i] = add(x[i], scl(p[i], a));
-    r[i] = sub(r[i], scl(q[i], a));
-}
-
-// dots = {<r, z>, <r, r>}: convergence test ||r||^2 <= tol2 * rr0 (rr0: the reference norm the
-// solver set), then the CG coefficient.
-static __global__ void k_cg_beta(CgS* S, const double* dots) {
-    if (threadIdx.x != 0 || S->done) return;
-    S->it += 1;
-    S->rr = dots[1];
-    if (!(dots[0] == dots[0]) || !(dots[1] == dots[1])) {
-        S->status = -4;
-        S->done = 1;
-        return;
-    }
-    if (S->rr <= S->tol2 * S->rr0) {
-        S->status = 0;
-        S->done = 1;
-        return;
-    }
-    if (S->it >= S->max_it) {
-        S->status = 1;
-        S->done = 1;
-        return;
-    }
-    S->b = dots[0] / S->rz;
-    S->rz = dots[0];
-}
-
-template <typename T>
-__global__ void k_cg_dir(C2<T>* p, const C2<T>* z, const CgS* S, int64_t N) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= N || S->done) return;
-    p[i] = add(z[i], scl(p[i], (T)S->b));
-}
-
 inline unsigned nblk(int64_t n) { return (unsigned)((n + 255) / 256); }
 
 // dst[k] = h^d sum conj(a_k) b_k (real part, or imaginary part where i_k), k < nq <= 2, over N points.

@@ -8,18 +8,9 @@
 
 #include "internal.hpp"
 #include "launch.hpp"
+#include "symbols.hpp"
 
 namespace gpe {
-
-// Rotation coefficient of the directional symbol along AX for the line (i1, i2):
-// R = -omega L_z = i omega (x d_y - y d_x) acts as +omega y xi along x and -omega x mu along y.
-template <int AX>
-__device__ __forceinline__ double rot_coef(const Geo& g, const LineCtx& lc, double omega) {
-    if (g.dim < 2 || omega == 0.0) return 0.0;
-    if (AX == 0) return omega * coord_of(lc.i1, g.L[1], g.h[1]);
-    if (AX == 1) return -omega * coord_of(lc.i1, g.L[0], g.h[0]);
-    return 0.0;
-}
 
 // ---------------------------------------------------------------------------------------------
 // Directional part of L (and H): out = acc + F_a^{-1}[sigma_a F_a f], sigma_a = xi^2/2 + rot*xi,
@@ -474,12 +465,6 @@ hipError_t op_lambda_tilde(const double* parts, double* dst, hipStream_t s) {
 // The spectral multiplier 1/(alpha + |k|^2/2) (with the 1/N of the inverse transforms) is applied
 // in the pass that does both the forward and the inverse transform (the last axis).
 // ---------------------------------------------------------------------------------------------
-template <typename T>
-__device__ __forceinline__ T pv_scale(int kind, double alpha, T V, T rho, double beta) {
-    const double d = alpha + (double)V + beta * (double)rho;
-    return kind == 1 ? (T)(1.0 / sqrt(d)) : (T)(1.0 / d);
-}
-
 template <typename T, int AX, bool F, bool I>
 struct OpPre {
     static constexpr bool FWD = F, INV = I, SCALARS = false, PREFETCH = true, WIDE = false;
@@ -569,6 +554,43 @@ __global__ void k_precond_diag(const C2<T>* r, C2<T>* out, const C2<T>* phi, con
     out[i] = v;
 }
 
+// The middle passes of P_Delta on a field transformed along x, in place: forward y (z), the multiplier
+// 1/(alpha + |k|^2/2) with the 1/N of the inverse transforms, inverse (z) y.
+template <typename T>
+static hipError_t kinetic_middle(const Geo& g, const Twiddles& tw, C2<T>* w, const double* alpha, hipStream_t s) {
+    const bool f64 = sizeof(T) == 8;
+    Partials none{nullptr, 0, 0, 0};
+    hipError_t e;
+    if (g.dim == 2) {
+        OpPre<T, 1, true, true> y{w, w, nullptr, nullptr, alpha, 0.0, 0, 0};
+        return launch_pass<T, 1>(g, 1, tw.get(1, f64), y, none, s);
+    }
+    OpPre<T, 1, true, false> y1{w, w, nullptr, nullptr, alpha, 0.0, 0, 0};
+    if ((e = launch_pass<T, 1>(g, 1, tw.get(1, f64), y1, none, s)) != hipSuccess) return e;
+    OpPre<T, 2, true, true> z{w, w, nullptr, nullptr, alpha, 0.0, 0, 0};
+    if ((e = launch_pass<T, 2>(g, 1, tw.get(2, f64), z, none, s)) != hipSuccess) return e;
+    OpPre<T, 1, false, true> y2{w, w, nullptr, nullptr, alpha, 0.0, 0, 0};
+    return launch_pass<T, 1>(g, 1, tw.get(1, f64), y2, none, s);
+}
+
+hipError_t op_kinetic_middle(const Geo& g, bool f64, const Twiddles& tw, void* w, const double* alpha_dev,
+                             hipStream_t s) {
+    return f64 ? kinetic_middle<double>(g, tw, (C2<double>*)w, alpha_dev, s)
+               : kinetic_middle<float>(g, tw, (C2<float>*)w, alpha_dev, s);
+}
+
+// The y part of L added to `out` (3-D: the pass between the first and the last), in place.
+hipError_t op_apply_y(const Geo& g, bool f64, const Twiddles& tw, const void* f, void* out, double omega,
+                      hipStream_t s) {
+    const Partials none{nullptr, 0, 0, 0};
+    if (f64) {
+        OpApply<double, 1> oy{(const C2<double>*)f, (const C2<double>*)out, (C2<double>*)out, nullptr, 0.0, omega, 0, 0};
+        return launch_pass<double, 1>(g, 1, tw.get(1, true), oy, none, s);
+    }
+    OpApply<float, 1> oy{(const C2<float>*)f, (const C2<float>*)out, (C2<float>*)out, nullptr, 0.0, omega, 0, 0};
+    return launch_pass<float, 1>(g, 1, tw.get(1, false), oy, none, s);
+}
+
 // Full multi-dimensional P_Delta with pre/post scalings: x forward, middle axes, x inverse.
 template <typename T>
 static hipError_t kinetic_chain(const Geo& g, const Twiddles& tw, const C2<T>* r, C2<T>* out, C2<T>* tmp,
@@ -583,17 +605,7 @@ static hipError_t kinetic_chain(const Geo& g, const Twiddles& tw, const C2<T>* r
     }
     OpPre<T, 0, true, false> x1{r, tmp, phi, V, alpha, beta, pre, 0};
     if ((e = launch_pass<T, 0>(g, 1, tw.get(0, f64), x1, none, s)) != hipSuccess) return e;
-    if (g.dim == 2) {
-        OpPre<T, 1, true, true> y{tmp, tmp, phi, V, alpha, beta, 0, 0};
-        if ((e = launch_pass<T, 1>(g, 1, tw.get(1, f64), y, none, s)) != hipSuccess) return e;
-    } else {
-        OpPre<T, 1, true, false> y1{tmp, tmp, phi, V, alpha, beta, 0, 0};
-        if ((e = launch_pass<T, 1>(g, 1, tw.get(1, f64), y1, none, s)) != hipSuccess) return e;
-        OpPre<T, 2, true, true> z{tmp, tmp, phi, V, alpha, beta, 0, 0};
-        if ((e = launch_pass<T, 2>(g, 1, tw.get(2, f64), z, none, s)) != hipSuccess) return e;
-        OpPre<T, 1, false, true> y2{tmp, tmp, phi, V, alpha, beta, 0, 0};
-        if ((e = launch_pass<T, 1>(g, 1, tw.get(1, f64), y2, none, s)) != hipSuccess) return e;
-    }
+    if ((e = kinetic_middle<T>(g, tw, tmp, alpha, s)) != hipSuccess) return e;
     OpPre<T, 0, false, true> x2{tmp, out, phi, V, alpha, beta, 0, post};
     return launch_pass<T, 0>(g, 1, tw.get(0, f64), x2, none, s);
 }

@@ -22,6 +22,8 @@
 
 namespace gpe {
 
+struct LinS;  // scalar state of the linear solvers
+
 struct LineCtx {
     int t;          // position of this thread within its line, [0, TPL)
     int c;          // line within the block
@@ -31,7 +33,8 @@ struct LineCtx {
     int64_t base;   // offset of point 0 of the line in the batched field
     int64_t stride; // distance between consecutive points of the line
     int64_t off_b;  // b * N
-    const Scal* sc; // the instance's scalar state in LDS (solver passes only)
+    const Scal* sc; // the instance's scalar state in LDS (PCG passes only)
+    const LinS* ls; // the same of the linear solvers' passes
     bool wave;      // every line of the workgroup lies within one wave (x passes, M <= 512)
     __device__ __forceinline__ int64_t at(int s) const { return base + (int64_t)(t + s * TPL) * stride; }
     __device__ __forceinline__ int k(int s) const { return t + s * TPL; }
@@ -188,6 +191,16 @@ struct IntakeOf<Op, true> {
     using type = typename Op::Intake;
 };
 
+// The scalar state a solver pass builds: Op::ScalarState when the Op names one, else the PCG's.
+template <class Op, class = void>
+struct ScalarStateOf {
+    using type = Scal;
+};
+template <class Op>
+struct ScalarStateOf<Op, std::void_t<typename Op::ScalarState>> {
+    using type = typename Op::ScalarState;
+};
+
 // Whether launches of an Op run without the occupancy cap (see pass_kernel): Op::WIDE, and for the
 // run-time-size transform (LG = 0) Op::WIDE_RT when the Op defines it.
 template <class Op, class = void>
@@ -289,10 +302,11 @@ void pass_kernel(Geo g, int C, const C2<T>* __restrict__ twg, Op op, Partials pr
         if constexpr (kEarlyInput) op.prefetch(g, lc, st);
     }
     if constexpr (Op::SCALARS) {
-        __shared__ Scal s_local;
+        using S = typename ScalarStateOf<Op>::type;
+        __shared__ S s_local;
         op.begin(g, lc.b, blk_in_inst, red, &s_local, in);  // all threads; ends with a barrier
         if (s_local.done) return;                       // uniform per block (one instance per block)
-        lc.sc = &s_local;
+        if constexpr (std::is_same_v<S, Scal>) lc.sc = &s_local; else lc.ls = &s_local;
     }
     if constexpr (EARLY && !kTwGlobal) {
         auto tw_put = [&](int j, C2<T> x) {

@@ -50,30 +50,6 @@ __global__ __launch_bounds__(256) void k_resid_diag(IterFields<T> f, const Scal*
 }
 
 // ---------------------------------------------------------------------------------------------
-// Collapse the per-block partial rows of each instance, kCollapseRows of them into one row in each
-// workgroup (fixed order), so that the consuming pass's workgroups reduce few rows.  The fold is
-// bound by one trip of the rows through memory: a workgroup reads its rows 16 lanes to a row, four
-// loads per thread in flight at once.  One workgroup per instance folding every row took 6.1 us for
-// the 1024 rows of a 128^3 pass and 8.0 us for its 3072 direction rows, this split 4.5 and 4.6 us (a launch
-// that does nothing takes about 2).
-// ---------------------------------------------------------------------------------------------
-constexpr int kCollapseRows = 64;
-template <int K, unsigned MASK>
-__global__ __launch_bounds__(256) void k_collapse(const double* parts, int nb, int stride, double* out, int split,
-                                                 int b0, const int* imap) {
-    __shared__ double red[(256 / 64) * 16];
-    __shared__ double tot[K];
-    const int bi = blockIdx.x / split, part = blockIdx.x - bi * split;
-    const int b = imap ? imap[bi] : b0 + bi;
-    const int first = part * kCollapseRows;
-    const Partials rows{const_cast<double*>(parts) + (size_t)first * K, min(kCollapseRows, nb - first), stride, 0};
-    RowFetch<K, kCollapseRows / 16, MASK> f;
-    f.issue(rows, b);
-    f.reduce(rows, b, red, tot);
-    for (int k = threadIdx.x; k < K; k += blockDim.x) out[((size_t)b * split + part) * K + k] = tot[k];
-}
-
-// ---------------------------------------------------------------------------------------------
 // Host: enqueue one iteration for B instances.
 // ---------------------------------------------------------------------------------------------
 template <typename T>
@@ -94,16 +70,8 @@ hipError_t enqueue_iteration(const IterCtx<T>& c, hipStream_t s) {
     };
     // the view a consumer absorbs: the region itself, or its collapse into a row per kCollapseRows
     auto consumable = [&](const Partials& p, int rc, int K) -> Partials {
-        if (p.nb <= kAbsorbRows) return p;
-        const int split = (p.nb + kCollapseRows - 1) / kCollapseRows;
-        const Partials q{c.parts + (size_t)rc * c.region_doubles, split, split, 0};
-        if (K == A_K)
-            hipLaunchKernelGGL((k_collapse<A_K, A_MAXMASK>), dim3((unsigned)(Bl * split)), dim3(256), 0, s, p.parts,
-                               p.nb, p.row_stride(), q.parts, split, g.b0, g.imap);
-        else
-            hipLaunchKernelGGL((k_collapse<B_K, B_MAXMASK>), dim3((unsigned)(Bl * split)), dim3(256), 0, s, p.parts,
-                               p.nb, p.row_stride(), q.parts, split, g.b0, g.imap);
-        return q;
+        double* const to = c.parts + (size_t)rc * c.region_doubles;
+        return K == A_K ? absorbable<A_K, A_MAXMASK>(p, to, Bl, g, s) : absorbable<B_K, B_MAXMASK>(p, to, Bl, g, s);
     };
     const Partials none{nullptr, 0, 0, 0};
     // algorithmic bytes of a launch: `reals` real numbers of sizeof(T) per grid point and instance

@@ -25,7 +25,6 @@ struct IterFields {
 enum : int {
     R_A1 = 0, R_A3, R_B, R_A1C = R_B + 3, R_A3C, R_BC, R_COUNT  // R_B spans three regions (x, y, z passes)
 };
-constexpr int kAbsorbRows = 256;
 
 // Optional per-kernel timing of an iteration (gpe_pcg_profile): every launch of the iteration
 // records a start/stop event pair with the launch itself, which brackets that kernel's execution

@@ -34,6 +34,7 @@
 #include "internal.hpp"
 #include "launch.hpp"
 #include "pcg.hpp"
+#include "rows.hpp"
 
 namespace gpe {
 
@@ -421,104 +422,10 @@ __device__ __forceinline__ void fin_step(Scal& S, const double* t, int kb) {
     }
 }
 
-// ---------------------------------------------------------------------------------------------
-// Scalar-state helpers for the passes
-// ---------------------------------------------------------------------------------------------
-// The state of instance b travels as 16-byte chunks, one per thread, so that a block fetches it
-// in one round trip.
-constexpr int kScalChunks = (int)(sizeof(Scal) / sizeof(uint4));
-static_assert(sizeof(Scal) % sizeof(uint4) == 0, "Scal is copied in 16-byte chunks");
-
-// The state of instance b, fetched by the first threads (one chunk each) at the start of a pass
-// and stored into LDS in begin().
-struct StateChunk {
-    uint4 ch;
-    __device__ __forceinline__ void issue(const Scal* in, int b) {
-        if (threadIdx.x < kScalChunks) ch = reinterpret_cast<const uint4*>(in + b)[threadIdx.x];
-    }
-    __device__ __forceinline__ void store(const Scal* in, int b, Scal* s) const {
-        uint4* dst = reinterpret_cast<uint4*>(s);
-        if (threadIdx.x < kScalChunks) dst[threadIdx.x] = ch;
-        for (int c = threadIdx.x + blockDim.x; c < kScalChunks; c += blockDim.x)  // blocks < 28 threads
-            dst[c] = reinterpret_cast<const uint4*>(in + b)[c];
-    }
-};
-
-// The partial rows (K <= 16 sums) of instance b in a region, fetched at the start of a pass in an
-// (entry, row group) layout: thread t reads entry k = t % 16 of rows t / 16 + j G (G = blockDim / 16,
-// j < NV) into registers.  reduce() folds them (and any rows beyond NV G), combines the four row
-// groups of each wave by two exchanges and the waves through LDS, in a fixed order.  Blocks that
-// are not whole waves fetch nothing early and reduce row by row.  Rows may be stale (a region
-// whose sums are not pending), never out of bounds.
-template <int K, int NV, unsigned mask>
-struct RowFetch {
-    static_assert(K >= 1 && K <= 16, "up to 16 sums per row");
-    double v[NV];
-    __device__ __forceinline__ static bool fast() { return (blockDim.x & 63u) == 0; }
-    __device__ __forceinline__ void issue(const Partials& P, int b) {
-        if (!fast() || !P.parts || P.nb <= 0) return;
-        const int k = threadIdx.x & 15, grp = threadIdx.x >> 4, G = blockDim.x >> 4;
-        const double id = ((mask >> k) & 1u) ? -1e300 : 0.0;
-        const double* rows = P.parts + (size_t)b * P.row_stride() * K;
-        const int kc = k < K ? k : K - 1;
-#pragma unroll
-        for (int j = 0; j < NV; ++j) {
-            const int r = grp + j * G;
-            const double x = rows[(size_t)min(r, P.nb - 1) * K + kc];  // clamped: always in bounds
-            v[j] = (k < K && r < P.nb) ? x : id;
-        }
-    }
-    __device__ __forceinline__ void reduce(const Partials& P, int b, double* red, double* tot) const {
-        if (!P.parts || P.nb <= 0) {
-            for (int k = threadIdx.x; k < K; k += blockDim.x) tot[k] = ((mask >> k) & 1u) ? -1e300 : 0.0;
-            __syncthreads();
-            return;
-        }
-        const double* rows = P.parts + (size_t)b * P.row_stride() * K;
-        if (!fast()) {
-            reduce_partials<K, mask>(rows, P.nb, red, tot);
-            return;
-        }
-        const int k = threadIdx.x & 15, grp = threadIdx.x >> 4, G = blockDim.x >> 4;
-        const bool mx = (mask >> k) & 1u;
-        double a = v[0];
-#pragma unroll
-        for (int j = 1; j < NV; ++j) a = mx ? fmax(a, v[j]) : a + v[j];
-        if (k < K)
-            for (int r = grp + NV * G; r < P.nb; r += G) a = mx ? fmax(a, rows[(size_t)r * K + k]) : a + rows[(size_t)r * K + k];
-        double o;
-        partner_pair<16>(a, o);
-        a = mx ? fmax(a, o) : a + o;
-        partner_pair<32>(a, o);
-        a = mx ? fmax(a, o) : a + o;
-        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
-        if (lane < 16) red[wave * 16 + lane] = a;
-        __syncthreads();
-        if (threadIdx.x < K) {
-            double t = red[threadIdx.x];
-            for (int w = 1; w < nw; ++w) t = mx ? fmax(t, red[w * 16 + threadIdx.x]) : t + red[w * 16 + threadIdx.x];
-            tot[threadIdx.x] = t;
-        }
-        __syncthreads();
-    }
-};
-
-// What a pass that only reads the state fetches early.
-struct IntakeState {
-    StateChunk st;
-};
-// What a pass that absorbs a region of K-sum rows fetches early (NV rows per thread in registers).
+using StateChunk = StateChunkOf<Scal>;
+using IntakeState = IntakeStateOf<Scal>;
 template <int K, int NV, unsigned MASK>
-struct IntakeAbsorb {
-    StateChunk st;
-    RowFetch<K, NV, MASK> rows;
-};
-
-// Copy the fetched state into LDS and barrier.
-__device__ __forceinline__ void state_copy(const Scal* in, int b, Scal* s, const StateChunk& ch) {
-    ch.store(in, b, s);
-    __syncthreads();
-}
+using IntakeAbsorb = IntakeAbsorbOf<Scal, K, NV, MASK>;
 
 // Thread 0 runs the scalar logic `fn(S, totals)` on the LDS state, with the totals copied into
 // registers first (so that stores to the state cannot force reloads of them), then barrier.  Only
@@ -544,14 +451,6 @@ __device__ __forceinline__ void absorb_finish(const Scal* in, int b, int blk, Sc
     it.st.store(in, b, s);
     it.rows.reduce(P, b, red, tot);
     finish<K>(s, tot, blk, fn);
-}
-
-// Block 0 of the instance writes the LDS state to out[b] (after a barrier that made it final).
-__device__ __forceinline__ void state_publish(Scal* out, int b, int blk, const Scal* s) {
-    if (blk != 0) return;
-    const uint4* src = reinterpret_cast<const uint4*>(s);
-    uint4* dst = reinterpret_cast<uint4*>(out + b);
-    for (int c = threadIdx.x; c < kScalChunks; c += blockDim.x) dst[c] = src[c];
 }
 
 // The scan of the full line search on the first wave: lane k evaluates the energy change at
