@@ -50,7 +50,7 @@ __global__ __launch_bounds__(256) void k_resid_diag(IterFields<T> f, const Scal*
 }
 
 // ---------------------------------------------------------------------------------------------
-// Host: enqueue one iteration for B instances.
+// Host: enqueue one iteration for B instances (2-D and 3-D; 1-D: pcg_line.hip).
 // ---------------------------------------------------------------------------------------------
 template <typename T>
 hipError_t enqueue_iteration(const IterCtx<T>& c, hipStream_t s) {
@@ -83,7 +83,7 @@ hipError_t enqueue_iteration(const IterCtx<T>& c, hipStream_t s) {
     // within an instance's rows; the step absorbs them at the next iteration's start, through their
     // collapse when they are many.
     const int nbx = pass_blocks_per_field(g, 0, cb, c.B, true);
-    const int nby = g.dim >= 2 ? pass_blocks_per_field(g, 1, cb, c.B, true) : 0;
+    const int nby = pass_blocks_per_field(g, 1, cb, c.B, true);
     const int nbz = g.dim >= 3 ? pass_blocks_per_field(g, 2, cb, c.B, true) : 0;
     const int nbB = nbx + nby + nbz;
     double* const partsB = c.parts + (size_t)R_B * c.region_doubles;
@@ -110,17 +110,8 @@ hipError_t enqueue_iteration(const IterCtx<T>& c, hipStream_t s) {
         pres = consumable(pr, R_A1C, A_K);
         pdir = pres;
         dir_in = S_step;
-    } else if (g.dim == 1) {
-        OpResid<T, true> op{f, S_dir, S_step, sb, pre, post};
-        const Partials pa = region(R_A1, 0);
-        if ((e = launch_pass<T, 0>(g, c.B, c.tw->get(0, f64), op, pa, s,
-                tick("step_resid_precond_x", 21))) != hipSuccess)
-            return e;
-        pres = consumable(pa, R_A1C, A_K);
-        pdir = pres;
-        dir_in = S_step;
     } else {
-        OpResid<T, false> op{f, S_dir, S_step, sb, pre, post};
+        OpResid<T> op{f, S_dir, S_step, sb, pre};
         const Partials pa1r = region(R_A1, 0);
         if ((e = launch_pass<T, 0>(g, c.B, c.tw->get(0, f64), op, pa1r, s,
                 tick("step_resid_fwd_x", 17))) != hipSuccess)
@@ -154,12 +145,7 @@ hipError_t enqueue_iteration(const IterCtx<T>& c, hipStream_t s) {
         dir_in = S_res;
     }
     // ---- phase B ----
-    if (g.dim == 1) {
-        OpLp<T, 0, true, true> op{f, dir_in, S_dir, pres, pdir};
-        if ((e = launch_pass<T, 0>(g, c.B, c.tw->get(0, f64), op, pb0, s,
-                tick("dir_Lp_x_linesearch", 11))) != hipSuccess)
-            return e;
-    } else if (g.dim == 2) {
+    if (g.dim == 2) {
         OpLp<T, 0, true, false> ox{f, dir_in, S_dir, pres, pdir};
         if ((e = launch_pass<T, 0>(g, c.B, c.tw->get(0, f64), ox, pb0, s,
                 tick("dir_Lp_x", 11))) != hipSuccess)

@@ -162,7 +162,44 @@ __device__ __forceinline__ void cg_sums(double* acc, C2<T> r, C2<T> pr, C2<T> rp
     acc[A_PHIPHI] += (double)abs2(ph);
 }
 
+// Line-search sums at one point (A = |phi|^2, B = Re conj(phi) phat, C = |phat|^2; o = L phat).
+template <typename T>
+__device__ __forceinline__ void linesearch_sums(double* acc, C2<T> ph, C2<T> p, C2<T> o) {
+    const double A = abs2(ph), Bq = redot(ph, p), Cq = abs2(p);
+    acc[B_C] += (double)redot(p, o);
+    acc[B_B] += (double)redot(ph, o);
+    acc[B_AA] += A * A;
+    acc[B_AB] += A * Bq;
+    acc[B_ACA] += A * (Cq - A);
+    acc[B_CACA] += (Cq - A) * (Cq - A);
+    acc[B_CAB] += (Cq - A) * Bq;
+    acc[B_BB] += Bq * Bq;
+    acc[B_AC] += A * Cq;
+    acc[B_SB] += Bq;
+    acc[B_SC] += Cq;
+    if (!isfinite((double)o.x) || !isfinite((double)o.y)) acc[B_NF] = 1.0;
+}
+
+// One iteration of 2-D and 3-D instances (r and r_{n-1} trade places after it: the caller swaps them).
 template <typename T>
 hipError_t enqueue_iteration(const IterCtx<T>& c, hipStream_t s);
+// `iters` iterations of 1-D instances in one launch (pcg_line.hip); the residual is left in f.rp.
+template <typename T>
+hipError_t enqueue_line(const IterCtx<T>& c, int iters, hipStream_t s);
+
+// `iters` iterations, r and r_{n-1} swapped as they go.
+template <typename T>
+inline hipError_t enqueue_iterations(IterCtx<T>& c, int iters, hipStream_t s) {
+    if (c.g.dim == 1) return enqueue_line<T>(c, iters, s);
+    for (int k = 0; k < iters; ++k) {
+        const hipError_t e = enqueue_iteration<T>(c, s);
+        if (e != hipSuccess) return e;
+        C2<T>* const r = c.f.r;
+        c.f.r = c.f.rp;
+        c.f.rp = r;
+    }
+    return hipSuccess;
+}
+
 
 }  // namespace gpe

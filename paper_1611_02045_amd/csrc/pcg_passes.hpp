@@ -512,16 +512,14 @@ using IntakeA = IntakeAbsorb<A_K, kARowsPerThread, A_MAXMASK>;
 // ---------------------------------------------------------------------------------------------
 // Phase A, first pass (x): [step from the direction sums], the pending retraction applied to
 // phi and L phi, residual, ||r||_inf, fresh scalars, P_V^{1/2} (or P_V) prologue, forward x.
-// With ONE (1-D) the pass also applies the multiplier, the inverse and the epilogue, i.e. the
-// whole preconditioner and the CG reductions.
 // ---------------------------------------------------------------------------------------------
-template <typename T, bool ONE>
+template <typename T>
 struct OpResid {
     // FP32 2-D/3-D: capped at four workgroups per CU despite a small spill (measured faster than the
     // second round of workgroups the unconstrained allocation leaves on the batched 512^2 step);
     // the run-time-size transform would spill 208 bytes under the cap and runs unconstrained
     // (measured 15% faster on 640^2)
-    static constexpr bool FWD = true, INV = ONE, SCALARS = true, PREFETCH = true, WIDE = sizeof(T) == 8 || ONE;
+    static constexpr bool FWD = true, INV = false, SCALARS = true, PREFETCH = true, WIDE = sizeof(T) == 8;
     static constexpr bool WIDE_RT = true;
     static constexpr int K = A_K;
     static constexpr unsigned MAXMASK = A_MAXMASK;
@@ -529,14 +527,12 @@ struct OpResid {
     const Scal* Sin;  // S_dir
     Scal* Sout;       // S_step
     Partials pb;      // the direction passes' rows (consumer view)
-    int pre, post;
+    int pre;
     using Intake = IntakeStep;
     __device__ void intake(int b, int, Intake& it) const { intake_step(Sin, pb, b, it); }
     struct State {
         C2<T> ph[8], lph[8], pp[8], lp[8];
         T V[8];
-        C2<T> r[ONE ? 8 : 1];
-        double d[ONE ? 8 : 1];
     };
     __device__ void prefetch(const Geo&, const LineCtx& lc, State& st) const {
 #pragma unroll
@@ -569,39 +565,14 @@ struct OpResid {
             res_sums<T>(acc, r);
             const double d = pv_diag(s, (double)V, (double)rho);
             v[q] = scl(r, pscale<T>(pre, d));
-            if constexpr (ONE) {
-                st.ph[q] = ph;
-                st.r[q] = r;
-                st.d[q] = d;
-            }
         }
     }
     template <int LG>
-    __device__ void spectral(const Geo&, const LineCtx& lc, State&, C2<T> (&v)[8], double (&)[K], C2<T>*,
-                             const C2<T>*) const {
-        if constexpr (ONE) {
-            const Scal& s = *lc.sc;
-            const double invN = 1.0 / lc.M;  // 1/M (exact for M = 2^k)
+    __device__ void spectral(const Geo&, const LineCtx&, State&, C2<T> (&)[8], double (&)[K], C2<T>*,
+                             const C2<T>*) const {}
+    __device__ void store(const Geo&, const LineCtx& lc, State&, C2<T> (&v)[8], double (&)[K]) const {
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const double k = freq_of(lc.k(q), lc.M, s.dk[0]);
-                v[q] = scl(v[q], (T)(invN / (s.lamt + 0.5 * k * k)));
-            }
-        }
-    }
-    __device__ void store(const Geo&, const LineCtx& lc, State& st, C2<T> (&v)[8], double (&acc)[K]) const {
-        if constexpr (!ONE) {
-#pragma unroll
-            for (int q = 0; q < 8; ++q) f.w[lc.at(q)] = v[q];
-        } else {
-#pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                const int64_t i = lc.at(q);
-                const C2<T> pr = scl(v[q], pscale<T>(post, st.d[q]));
-                f.pr[i] = pr;
-                cg_sums<T>(acc, st.r[q], pr, f.rp[i], f.pp[i], st.ph[q]);
-            }
-        }
+        for (int q = 0; q < 8; ++q) f.w[lc.at(q)] = v[q];
     }
 };
 
@@ -866,22 +837,8 @@ struct OpLp {
             if constexpr (!LAST) {
                 f.w[i] = o;
             } else {
-                const C2<T> ph = st.ph[q], p = st.p[q];
                 f.lp[i] = o;
-                // line-search sums (A = |phi|^2, B = Re conj(phi) phat, C = |phat|^2)
-                const double A = abs2(ph), Bq = redot(ph, p), Cq = abs2(p);
-                acc[B_C] += (double)redot(p, o);
-                acc[B_B] += (double)redot(ph, o);
-                acc[B_AA] += A * A;
-                acc[B_AB] += A * Bq;
-                acc[B_ACA] += A * (Cq - A);
-                acc[B_CACA] += (Cq - A) * (Cq - A);
-                acc[B_CAB] += (Cq - A) * Bq;
-                acc[B_BB] += Bq * Bq;
-                acc[B_AC] += A * Cq;
-                acc[B_SB] += Bq;
-                acc[B_SC] += Cq;
-                if (!isfinite((double)o.x) || !isfinite((double)o.y)) acc[B_NF] = 1.0;
+                linesearch_sums<T>(acc, st.ph[q], st.p[q], o);
             }
         }
     }
@@ -889,9 +846,8 @@ struct OpLp {
 
 // Every pass of the iteration for one precision: X(AX, Op).  Their launches are compiled in four
 // translation units (x or strided passes, per precision) to keep the build parallel.
-#define GPE_PCG_X_PASSES(X, T)                                                                                       \
-    X(T, 0, (OpResid<T, true>)) X(T, 0, (OpResid<T, false>)) X(T, 0, (OpPLast<T>)) X(T, 0, (OpLp<T, 0, true, true>)) \
-    X(T, 0, (OpLp<T, 0, true, false>))
+#define GPE_PCG_X_PASSES(X, T) \
+    X(T, 0, (OpResid<T>)) X(T, 0, (OpPLast<T>)) X(T, 0, (OpLp<T, 0, true, false>))
 #define GPE_PCG_YZ_PASSES(X, T)                                                                                  \
     X(T, 1, (OpPMid<T, 1, true, true, true>)) X(T, 1, (OpPMid<T, 1, true, false, true>))                         \
     X(T, 2, (OpPMid<T, 2, true, true, false>)) X(T, 1, (OpPMid<T, 1, false, true, false>))                       \

@@ -284,7 +284,8 @@ hipError_t run_phase(PhaseArgs& pa, IterFields<T> f, std::vector<Scal>& host_S, 
     // Graph capture is not possible on the legacy default stream (the usual caller's stream): with
     // graphs the phase runs on a private stream that first waits for the caller's queued work; the
     // loop below ends with a synchronisation of that stream, so nothing is left queued on it.
-    const bool want_graph = pa.use_graph && pa.check_every % 2 == 0;
+    // (1-D: a chunk is one launch, with nothing to capture)
+    const bool want_graph = pa.use_graph && pa.check_every % 2 == 0 && g.dim > 1;
     PrivateStream own;
     hipStream_t s = s_caller;
     if (want_graph) {
@@ -343,23 +344,13 @@ hipError_t run_phase(PhaseArgs& pa, IterFields<T> f, std::vector<Scal>& host_S, 
         if (queued > 2 * max_iter + 4 * (int64_t)pa.check_every + 64) return hipErrorUnknown;
         queued += pa.check_every;
         if (!graph.exec && want_graph && chunks >= 1) {
-            if ((e = graph.capture(s, [&] {
-                     for (int k = 0; k < pa.check_every; ++k) {
-                         hipError_t ee = enqueue_iteration<T>(c, s);
-                         if (ee != hipSuccess) return ee;
-                         std::swap(c.f.r, c.f.rp);
-                     }
-                     return hipSuccess;
-                 })) != hipSuccess)
+            if ((e = graph.capture(s, [&] { return enqueue_iterations<T>(c, pa.check_every, s); })) != hipSuccess)
                 return e;
         }
         if (graph.exec) {
             if ((e = graph.launch(s)) != hipSuccess) return e;
         } else {
-            for (int k = 0; k < pa.check_every; ++k) {
-                if ((e = enqueue_iteration<T>(c, s)) != hipSuccess) return e;
-                std::swap(c.f.r, c.f.rp);
-            }
+            if ((e = enqueue_iterations<T>(c, pa.check_every, s)) != hipSuccess) return e;
         }
         ++chunks;
         since_refresh += pa.check_every;
@@ -454,9 +445,8 @@ hipError_t profile_phase(PhaseArgs& pa, IterFields<T> f, std::vector<Scal>& host
     c.pointwise_blocks = (int)std::max<int64_t>(1, std::min<int64_t>(1024, N / 1024));
     c.timer = &timer;
     for (int k = 0; k < iters; ++k) {
-        if ((e = enqueue_iteration<T>(c, s)) != hipSuccess) return e;
+        if ((e = enqueue_iterations<T>(c, 1, s)) != hipSuccess) return e;
         if ((e = timer.collect()) != hipSuccess) return e;
-        std::swap(c.f.r, c.f.rp);
     }
     return hipMemcpy(host_S.data(), S_dir, sizeof(Scal) * pa.B, hipMemcpyDeviceToHost);
 }
