@@ -82,6 +82,10 @@ int gpe_plan_destroy(gpe_plan_t* plan);
 int gpe_energy(gpe_plan_t* plan, const void* phi, const void* V, double* E, double* parts,
                void* stream);
 
+/* gpe_energy with the value also written to E_dev (device, one scalar of the plan's real type), for programs
+ * that keep it there.  Synchronises. */
+int gpe_energy_value(gpe_plan_t* plan, const void* phi, const void* V, void* E_dev, double* E, void* stream);
+
 /* Hphi = H_phi phi = -1/2 Delta phi + V phi + beta |phi|^2 phi - omega L_z phi (Section 2
  * mean-field Hamiltonian, Section 3 discretisation).  Device pointers; Hphi must not alias phi.
  * Asynchronous. */
@@ -93,7 +97,8 @@ int gpe_apply_H_batched(gpe_plan_t* plan, int count, const void* phi, const void
                         void* stream);
 
 /* Kernel choice of every H apply (gpe_apply_H, gpe_apply_H_batched, the noalloc form, and the
- * applies inside the solvers, the backward-Euler steps and the adjoint), process-wide:
+ * whole applies inside the solvers; the iterations' own passes, the linear CG's and the energy gradient's
+ * are fused with other work and always directional), process-wide:
  *   GPE_APPLY_PASSES  directional passes: an x pass (with the pointwise part) into a workspace, then
  *                     a y pass (and a z pass) adding theirs: 11sN bytes in 2-D (s bytes per real, N
  *                     points), 17sN in 3-D;
@@ -271,6 +276,11 @@ int gpe_be_solve(gpe_plan_t* plan, const void* V, void* phi_inout, double dt, in
  * Synchronises when a host scalar is requested. */
 int gpe_energy_grad(gpe_plan_t* plan, const void* phi, const void* V, void* grad_phi, void* grad_V,
                     double* dE_dbeta, double* dE_domega, void* stream);
+
+/* gpe_energy_grad times the device scalar *gE (the plan's real type), every result on the device: grad_V
+ * (nullable), dE_dbeta and dE_domega (one scalar of the plan's real type each, nullable).  Asynchronous. */
+int gpe_energy_grad_scaled(gpe_plan_t* plan, const void* phi, const void* V, const void* gE, void* grad_phi,
+                           void* grad_V, void* dE_dbeta, void* dE_domega, void* stream);
 
 /* Implicit adjoint at a converged ground state phi_star: solves A mu = M rhs on the tangent
  * space {f : Re<phi_star, f> = Re<i phi_star, f> = 0} with A = Pi (1/2 nabla^2 E - lambda) Pi,

@@ -61,17 +61,20 @@ class Energy(torch.autograd.Function):
         V = V.detach().contiguous()
         b, o = float(beta), float(omega)
         plan = plan_for(grid, b, o, _dtype(phi))
-        E = plan.energy(phi, V)
+        E = plan.energy_value(phi, V)
         ctx.save_for_backward(phi, V)
         ctx.grid, ctx.b, ctx.o = grid, b, o
-        return torch.tensor(E, dtype=V.dtype, device=V.device)
+        return E
 
     @staticmethod
     def backward(ctx, gE):
         phi, V = ctx.saved_tensors
         plan = plan_for(ctx.grid, ctx.b, ctx.o, _dtype(phi))
-        gphi, gV, db, do = plan.energy_grad(phi, V)
         g = gE.to(V.dtype)
+        if not torch.is_grad_enabled():
+            # every gradient times g in the passes of one H apply; nothing returns to the host
+            return (*plan.energy_grad_scaled(phi, V, g), None)
+        gphi, gV, db, do = plan.energy_grad(phi, V)  # create_graph: keep the products with g differentiable
         return (g * gphi, g * gV, g * torch.tensor(db, dtype=V.dtype, device=V.device),
                 g * torch.tensor(do, dtype=V.dtype, device=V.device), None)
 

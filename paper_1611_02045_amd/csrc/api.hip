@@ -175,6 +175,11 @@ int gpe_plan_create(const gpe_problem_t* prob, int dtype, gpe_plan_t** out) {
     hipError_t e = build_twiddles(p->g, p->tw);
     if (e == hipSuccess) e = reduce_init(p->red, 1, 16, 1 << 18);
     if (e == hipSuccess) e = hipGetDevice(&p->device);
+    if (e == hipSuccess) {
+        std::lock_guard<std::mutex> lock(capture_mutex());
+        e = hipHostMalloc((void**)&p->host, sizeof(double) * kHostScalars, hipHostMallocMapped);
+        if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&p->host_dev, p->host, 0);
+    }
     if (e != hipSuccess) {
         set_error(std::string("plan creation failed: ") + hipGetErrorString(e));
         p->release();
@@ -196,21 +201,35 @@ int gpe_plan_destroy(gpe_plan_t* plan) {
     return GPE_OK;
 }
 
+// The energy (its parts in plan->host after the synchronisation) and, with E_dev, its value on the device.
+static int energy_impl(gpe_plan_t* plan, const void* phi, const void* V, void* E_dev, double* E, double* parts,
+                       void* stream) {
+    hipStream_t s = (hipStream_t)stream;
+    HIPCHK(op_energy(plan->g, plan->f64(), plan->tw, phi, V, plan->prob.beta, plan->prob.omega, plan->red,
+                     (double*)plan->red.scalars.ptr, s, plan->host_dev, E_dev));
+    HIPCHK(hipStreamSynchronize(s));
+    const double* h = plan->host;
+    *E = h[0] + h[1] + h[2] + h[3];
+    if (parts) std::memcpy(parts, h, 4 * sizeof(double));
+    if (!std::isfinite(*E)) { set_error("energy is not finite"); return GPE_ENONFINITE; }
+    return GPE_OK;
+}
+
 int gpe_energy(gpe_plan_t* plan, const void* phi, const void* V, double* E, double* parts, void* stream) {
     NEEDPTR(plan, "plan");
     NEEDPTR(phi, "phi");
     NEEDPTR(V, "V");
     NEEDPTR(E, "E");
-    hipStream_t s = (hipStream_t)stream;
-    double* dst = (double*)plan->red.scalars.ptr;
-    HIPCHK(op_energy(plan->g, plan->f64(), plan->tw, phi, V, plan->prob.beta, plan->prob.omega, plan->red, dst, s));
-    double h[4];
-    HIPCHK(hipMemcpyAsync(h, dst, sizeof(h), hipMemcpyDeviceToHost, s));
-    HIPCHK(hipStreamSynchronize(s));
-    *E = h[0] + h[1] + h[2] + h[3];
-    if (parts) std::memcpy(parts, h, sizeof(h));
-    if (!std::isfinite(*E)) { set_error("energy is not finite"); return GPE_ENONFINITE; }
-    return GPE_OK;
+    return energy_impl(plan, phi, V, nullptr, E, parts, stream);
+}
+
+int gpe_energy_value(gpe_plan_t* plan, const void* phi, const void* V, void* E_dev, double* E, void* stream) {
+    NEEDPTR(plan, "plan");
+    NEEDPTR(phi, "phi");
+    NEEDPTR(V, "V");
+    NEEDPTR(E_dev, "E_dev");
+    NEEDPTR(E, "E");
+    return energy_impl(plan, phi, V, E_dev, E, nullptr, stream);
 }
 
 int gpe_apply_H_batched(gpe_plan_t* plan, int count, const void* phi, const void* V, void* Hphi, void* stream) {
@@ -328,23 +347,30 @@ int gpe_energy_grad(gpe_plan_t* plan, const void* phi, const void* V, void* grad
     if (grad_phi == phi) { set_error("grad_phi must not alias phi"); return GPE_EINVAL; }
     hipStream_t s = (hipStream_t)stream;
     const size_t cb = plan->f64() ? 16 : 8;
+    const bool scalars = dE_dbeta || dE_domega;
     HIPCHK(plan->tmp.ensure(cb * (size_t)plan->g.N));
-    // dE/dphi (conjugate Wirtinger, real loss) = 2 h^d H_phi phi: apply H then scale.
-    HIPCHK(op_apply(plan->g, plan->f64(), 1, plan->tw, phi, V, grad_phi, plan->tmp.ptr, plan->prob.beta,
-                    plan->prob.omega, true, s));
-    HIPCHK(op_scale_complex(plan->g, plan->f64(), grad_phi, 2.0 * plan->g.cell, plan->g.N, s));
-    if (grad_V) HIPCHK(op_density(plan->g, plan->f64(), phi, grad_V, plan->g.cell, s));
-    if (dE_dbeta || dE_domega) {
-        // With beta = omega = 1 the energy parts are exactly 1/2 h^d sum|phi|^4 = dE/dbeta and
-        // <phi, (-L_z) phi> = dE/domega (E is affine in beta and in omega).
-        double* dst = (double*)plan->red.scalars.ptr;
-        HIPCHK(op_energy(plan->g, plan->f64(), plan->tw, phi, V, 1.0, plan->g.dim >= 2 ? 1.0 : 0.0, plan->red, dst, s));
-        double h[4];
-        HIPCHK(hipMemcpyAsync(h, dst, sizeof(h), hipMemcpyDeviceToHost, s));
+    HIPCHK(op_energy_grad(plan->g, plan->f64(), plan->tw, phi, V, grad_phi, grad_V, plan->prob.beta, plan->prob.omega,
+                          plan->red, scalars ? plan->host_dev : nullptr, nullptr, nullptr, nullptr, plan->tmp.ptr, s));
+    if (scalars) {
         HIPCHK(hipStreamSynchronize(s));
-        if (dE_dbeta) *dE_dbeta = h[2];
-        if (dE_domega) *dE_domega = h[3];
+        if (dE_dbeta) *dE_dbeta = plan->host[0];
+        if (dE_domega) *dE_domega = plan->host[1];
     }
+    return GPE_OK;
+}
+
+int gpe_energy_grad_scaled(gpe_plan_t* plan, const void* phi, const void* V, const void* gE, void* grad_phi,
+                           void* grad_V, void* dE_dbeta, void* dE_domega, void* stream) {
+    NEEDPTR(plan, "plan");
+    NEEDPTR(phi, "phi");
+    NEEDPTR(V, "V");
+    NEEDPTR(gE, "gE");
+    NEEDPTR(grad_phi, "grad_phi");
+    if (grad_phi == phi) { set_error("grad_phi must not alias phi"); return GPE_EINVAL; }
+    const size_t cb = plan->f64() ? 16 : 8;
+    HIPCHK(plan->tmp.ensure(cb * (size_t)plan->g.N));
+    HIPCHK(op_energy_grad(plan->g, plan->f64(), plan->tw, phi, V, grad_phi, grad_V, plan->prob.beta, plan->prob.omega,
+                          plan->red, nullptr, dE_dbeta, dE_domega, gE, plan->tmp.ptr, (hipStream_t)stream));
     return GPE_OK;
 }
 

@@ -91,9 +91,18 @@ hipError_t op_prolong(const Geo& g, bool f64, const Twiddles& tw, const void* in
 hipError_t op_autotune(const Geo& g, bool f64, int B, const Twiddles& tw, void* f, void* out, hipStream_t s,
                        int tiles[3], double us[3]);
 
-// Energy parts of one field: dst (device, 4 doubles) <- {kinetic, potential, interaction, rotation}.
+// Energy parts of one field: dst (device, 4 doubles) <- {kinetic, potential, interaction, rotation};
+// host: the same in mapped host memory; E: their sum, a device scalar of the field precision.
 hipError_t op_energy(const Geo& g, bool f64, const Twiddles& tw, const void* phi, const void* V,
-                     double beta, double omega, Reduce& red, double* dst, hipStream_t s);
+                     double beta, double omega, Reduce& red, double* dst, hipStream_t s, double* host = nullptr,
+                     void* E = nullptr);
+
+// Backward of the energy: gphi = 2 h^d H phi, gV = h^d |phi|^2 (nullable), and {dE/dbeta, dE/domega} into dst
+// (device, FP64, nullable) and the device scalars db, dw of the field precision (nullable); with gE (device
+// scalar of the field precision) every output but dst is multiplied by it.  tmp: one complex field (dim >= 2).
+hipError_t op_energy_grad(const Geo& g, bool f64, const Twiddles& tw, const void* phi, const void* V, void* gphi,
+                          void* gV, double beta, double omega, Reduce& red, double* dst, void* db, void* dw,
+                          const void* gE, void* tmp, hipStream_t s);
 
 // Preconditioner application with the shift read from device memory (*alpha_dev).
 hipError_t op_precond(const Geo& g, bool f64, const Twiddles& tw, int kind, const void* phi,
@@ -112,10 +121,6 @@ hipError_t op_min_diag(const Geo& g, bool f64, const void* phi, const void* V, c
 
 // lambda~ = kinetic + potential + 2 interaction from energy parts (device to device).
 hipError_t op_lambda_tilde(const double* parts, double* dst, hipStream_t s);
-
-// Energy gradient pieces: grad_phi = 2 h^d H phi (in place scaling of Hphi), grad_V = h^d |phi|^2.
-hipError_t op_scale_complex(const Geo& g, bool f64, void* x, double s, int64_t count, hipStream_t st);
-hipError_t op_density(const Geo& g, bool f64, const void* phi, void* out, double scale, hipStream_t s);
 
 // Thread-local error message.
 void set_error(const std::string& msg);

@@ -396,9 +396,12 @@ struct OpEnergy {
     }
 };
 
-// Sum the per-block partials of up to three passes and scale into {kin, pot, inter, rot}.
-__global__ void k_energy_collect(const double* p0, int n0, const double* p1, int n1, const double* p2, int n2,
-                                 double cell, double beta, double* dst) {
+// Sum the per-block partials of up to three passes and scale into {kin, pot, inter, rot}.  host
+// (nullable): the same in mapped host memory; E (nullable): their sum in the field precision.
+template <typename T>
+__global__ __launch_bounds__(256) void k_energy_collect(const double* p0, int n0, const double* p1, int n1,
+                                                        const double* p2, int n2, double cell, double beta,
+                                                        double* dst, double* host, T* E) {
     __shared__ double red[16 * 4 + 8];
     double v[4] = {0, 0, 0, 0};
     const double* ps[3] = {p0, p1, p2};
@@ -411,16 +414,21 @@ __global__ void k_energy_collect(const double* p0, int n0, const double* p1, int
     __shared__ double T4[4];
     block_reduce<4>(v, red, T4);
     if (threadIdx.x == 0) {
-        dst[0] = cell * T4[0];               // <phi, T phi>
-        dst[1] = cell * T4[2];               // <phi, V phi>
-        dst[2] = 0.5 * beta * cell * T4[3];  // beta/2 h^d sum |phi|^4
-        dst[3] = cell * T4[1];               // <phi, R phi> = -omega Re<phi, L_z phi>
+        const double h[4] = {cell * T4[0],                // <phi, T phi>
+                             cell * T4[2],                // <phi, V phi>
+                             0.5 * beta * cell * T4[3],   // beta/2 h^d sum |phi|^4
+                             cell * T4[1]};               // <phi, R phi> = -omega Re<phi, L_z phi>
+        for (int k = 0; k < 4; ++k) {
+            dst[k] = h[k];
+            if (host) host[k] = h[k];
+        }
+        if (E) *E = (T)(h[0] + h[1] + h[2] + h[3]);
     }
 }
 
 template <typename T>
 static hipError_t energy_t(const Geo& g, const Twiddles& tw, const void* phi, const void* V, double beta,
-                           double omega, Reduce& red, double* dst, hipStream_t s) {
+                           double omega, Reduce& red, double* dst, double* host, void* E, hipStream_t s) {
     const bool f64 = sizeof(T) == 8;
     const int cb = (int)sizeof(C2<T>);
     const C2<T>* P = (const C2<T>*)phi;
@@ -440,15 +448,156 @@ static hipError_t energy_t(const Geo& g, const Twiddles& tw, const void* phi, co
         nn[ax] = nb;
         off += (size_t)nb * 4;
     }
-    hipLaunchKernelGGL(k_energy_collect, dim3(1), dim3(256), 0, s, pp[0], nn[0], pp[1], nn[1], pp[2], nn[2],
-                       g.cell, beta, dst);
+    hipLaunchKernelGGL(k_energy_collect<T>, dim3(1), dim3(256), 0, s, pp[0], nn[0], pp[1], nn[1], pp[2], nn[2],
+                       g.cell, beta, dst, host, (T*)E);
     return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------------------------
+// Backward of the energy in the passes of one H apply: the gradient 2 h^d H phi (the last pass scales
+// what it writes), h^d |phi|^2 and the sums of dE/dbeta = h^d/2 sum |phi|^4 (x pass) and dE/domega = <phi, -L_z phi>
+// (Parseval, on the transforms that the apply makes anyway).  E is affine in beta and omega, so both
+// derivatives are the energy's own sums at beta = omega = 1.  gE (nullable): a factor in device memory.
+// A separate apply, scaling, density and energy took 8 launches and 23 s N bytes in 2-D against 3 launches
+// and 12 s N here: 640^2 FP64, 58 us of kernels then, 32 now.
+// ---------------------------------------------------------------------------------------------
+template <typename T, int AX, bool LAST>
+struct OpEnergyGrad {
+    static constexpr bool FWD = true, INV = true, SCALARS = false, PREFETCH = true, WIDE = false;
+    static constexpr int K = AX < 2 ? 2 : 0;  // {quartic, rotation}
+    static constexpr int KA = K > 0 ? K : 1;
+    static constexpr unsigned MAXMASK = 0;
+    static constexpr bool PW = AX == 0;
+    const C2<T>* f;
+    const C2<T>* acc;  // strided passes: the running sum
+    C2<T>* out;
+    const T* V;
+    T* gV;             // x pass, nullable
+    const T* gE;       // nullable
+    double beta, omega;
+    struct State {
+        C2<T> f0[8];
+        C2<T> a[PW ? 1 : 8];
+        T V[PW ? 8 : 1];
+    };
+    __device__ void prefetch(const Geo&, const LineCtx& lc, State& st) const {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) st.f0[s] = f[lc.at(s)];
+    }
+    __device__ void prefetch_tail(const Geo&, const LineCtx& lc, State& st) const {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            if constexpr (PW) st.V[s] = V[lc.at(s)];
+            if constexpr (!PW) st.a[s] = acc[lc.at(s)];
+        }
+    }
+    __device__ void load(const Geo&, const LineCtx&, State& st, C2<T> (&v)[8], double (&)[KA]) const {
+#pragma unroll
+        for (int s = 0; s < 8; ++s) v[s] = st.f0[s];
+    }
+    template <int LG>
+    __device__ void spectral(const Geo& g, const LineCtx& lc, State&, C2<T> (&v)[8], double (&sum)[KA], C2<T>*,
+                             const C2<T>*) const {
+        const double one = rot_coef<AX>(g, lc, 1.0);  // rotation symbol at omega = 1
+        const double rot = rot_coef<AX>(g, lc, omega);
+        const double inv = 1.0 / lc.M;  // 1/M (exact for M = 2^k)
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const double xi = freq_of(lc.k(s), lc.M, g.dk[AX]);
+            if constexpr (K > 0) sum[1] += one * xi * ((double)abs2(v[s]) * inv);
+            v[s] = scl(v[s], (T)((0.5 * xi * xi + rot * xi) * inv));
+        }
+    }
+    __device__ void store(const Geo& g, const LineCtx& lc, State& st, C2<T> (&v)[8], double (&sum)[KA]) const {
+        const T scale = (T)(2.0 * g.cell), cell = (T)g.cell;
+        const T ge = gE ? *gE : (T)1;
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            const int64_t i = lc.at(s);
+            C2<T> o = v[s];
+            if constexpr (PW) {
+                const T r = abs2(st.f0[s]);
+                o = add(o, scl(st.f0[s], st.V[s] + (T)beta * r));
+                sum[0] += (double)r * (double)r;
+                if (gV) gV[i] = gE ? ge * (cell * r) : cell * r;
+            } else {
+                o = add(o, st.a[s]);
+            }
+            if constexpr (LAST) {
+                o = scl(o, scale);
+                if (gE) o = scl(o, ge);
+            }
+            out[i] = o;
+        }
+    }
+};
+
+// {dE/dbeta, dE/domega} from the partial rows of the x and y passes, into dst (FP64) or, times *gE, into the
+// field-precision scalars db and dw (nullable).
+template <typename T>
+__global__ __launch_bounds__(256) void k_grad_collect(const double* p0, int n0, const double* p1, int n1, double cell,
+                                                      double* dst, T* db, T* dw, const T* gE) {
+    __shared__ double red[8 * 2];
+    double v[2] = {0.0, 0.0};
+    for (int i = threadIdx.x; i < n0; i += blockDim.x) {
+        v[0] += p0[2 * (size_t)i];
+        v[1] += p0[2 * (size_t)i + 1];
+    }
+    for (int i = threadIdx.x; i < n1; i += blockDim.x) v[1] += p1[2 * (size_t)i + 1];
+    block_reduce_to<2, 0u>(v, red, [=](int k, double t) {
+        const double x = k == 0 ? 0.5 * cell * t : cell * t;
+        if (dst) dst[k] = x;
+        T* const to = k == 0 ? db : dw;
+        if (to) *to = gE ? *gE * (T)x : (T)x;
+    });
+}
+
+template <typename T>
+static hipError_t energy_grad_t(const Geo& g, const Twiddles& tw, const void* phi, const void* V, void* gphi, void* gV,
+                                double beta, double omega, Reduce& red, double* dst, void* db, void* dw,
+                                const void* gE, void* tmp, hipStream_t s) {
+    const bool f64 = sizeof(T) == 8;
+    const int cb = (int)sizeof(C2<T>);
+    const C2<T>* F = (const C2<T>*)phi;
+    C2<T>*const O = (C2<T>*)gphi, *const W = (C2<T>*)tmp;
+    const T *const Vt = (const T*)V, *const ge = (const T*)gE;
+    const int n0 = pass_blocks_per_field(g, 0, cb, 1, false), n1 = g.dim > 1 ? pass_blocks_per_field(g, 1, cb, 1, false) : 0;
+    double* const p0 = (double*)red.parts.ptr;
+    double* const p1 = p0 + 2 * (size_t)n0;
+    const Partials r0{p0, n0, n0, 0}, r1{p1, n1, n1, 0}, none{nullptr, 0, 0, 0};
+    hipError_t e;
+    if (g.dim == 1) {
+        OpEnergyGrad<T, 0, true> ox{F, nullptr, O, Vt, (T*)gV, ge, beta, omega};
+        e = launch_pass<T, 0>(g, 1, tw.get(0, f64), ox, r0, s);
+    } else {
+        OpEnergyGrad<T, 0, false> ox{F, nullptr, W, Vt, (T*)gV, ge, beta, omega};
+        e = launch_pass<T, 0>(g, 1, tw.get(0, f64), ox, r0, s);
+        if (e == hipSuccess && g.dim == 2) {
+            OpEnergyGrad<T, 1, true> oy{F, W, O, nullptr, nullptr, ge, beta, omega};
+            e = launch_pass<T, 1>(g, 1, tw.get(1, f64), oy, r1, s);
+        } else if (e == hipSuccess) {
+            OpEnergyGrad<T, 1, false> oy{F, W, W, nullptr, nullptr, ge, beta, omega};
+            e = launch_pass<T, 1>(g, 1, tw.get(1, f64), oy, r1, s);
+            OpEnergyGrad<T, 2, true> oz{F, W, O, nullptr, nullptr, ge, beta, omega};
+            if (e == hipSuccess) e = launch_pass<T, 2>(g, 1, tw.get(2, f64), oz, none, s);
+        }
+    }
+    if (e != hipSuccess || !(dst || db || dw)) return e;
+    hipLaunchKernelGGL(k_grad_collect<T>, dim3(1), dim3(256), 0, s, p0, n0, p1, n1, g.cell, dst, (T*)db, (T*)dw, ge);
+    return hipGetLastError();
+}
+
+hipError_t op_energy_grad(const Geo& g, bool f64, const Twiddles& tw, const void* phi, const void* V, void* gphi,
+                          void* gV, double beta, double omega, Reduce& red, double* dst, void* db, void* dw,
+                          const void* gE, void* tmp, hipStream_t s) {
+    return f64 ? energy_grad_t<double>(g, tw, phi, V, gphi, gV, beta, omega, red, dst, db, dw, gE, tmp, s)
+               : energy_grad_t<float>(g, tw, phi, V, gphi, gV, beta, omega, red, dst, db, dw, gE, tmp, s);
+}
+
 hipError_t op_energy(const Geo& g, bool f64, const Twiddles& tw, const void* phi, const void* V, double beta,
-                     double omega, Reduce& red, double* dst, hipStream_t s) {
-    return f64 ? energy_t<double>(g, tw, phi, V, beta, omega, red, dst, s)
-               : energy_t<float>(g, tw, phi, V, beta, omega, red, dst, s);
+                     double omega, Reduce& red, double* dst, hipStream_t s, double* host, void* E) {
+    return f64 ? energy_t<double>(g, tw, phi, V, beta, omega, red, dst, host, E, s)
+               : energy_t<float>(g, tw, phi, V, beta, omega, red, dst, host, E, s);
 }
 
 __global__ void k_lambda_tilde(const double* parts, double* dst) {
@@ -669,39 +818,6 @@ hipError_t op_min_diag(const Geo& g, bool f64, const void* phi, const void* V, c
         hipLaunchKernelGGL(k_min_diag<float>, dim3(blocks), dim3(256), 0, s, (const C2<float>*)phi,
                            (const float*)V, alpha_dev, beta, g.N, parts);
     hipLaunchKernelGGL(k_min_collect, dim3(1), dim3(256), 0, s, parts, blocks, dst);
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------------------------
-// Small pointwise helpers.
-// ---------------------------------------------------------------------------------------------
-template <typename T>
-__global__ void k_scale_complex(C2<T>* x, T s, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) x[i] = scl(x[i], s);
-}
-
-template <typename T>
-__global__ void k_density(const C2<T>* phi, T* out, T scale, int64_t n) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) out[i] = scale * abs2(phi[i]);
-}
-
-hipError_t op_scale_complex(const Geo&, bool f64, void* x, double s, int64_t count, hipStream_t st) {
-    const unsigned blocks = (unsigned)((count + 255) / 256);
-    if (f64) hipLaunchKernelGGL(k_scale_complex<double>, dim3(blocks), dim3(256), 0, st, (C2<double>*)x, s, count);
-    else hipLaunchKernelGGL(k_scale_complex<float>, dim3(blocks), dim3(256), 0, st, (C2<float>*)x, (float)s, count);
-    return hipGetLastError();
-}
-
-hipError_t op_density(const Geo& g, bool f64, const void* phi, void* out, double scale, hipStream_t s) {
-    const unsigned blocks = (unsigned)((g.N + 255) / 256);
-    if (f64)
-        hipLaunchKernelGGL(k_density<double>, dim3(blocks), dim3(256), 0, s, (const C2<double>*)phi, (double*)out,
-                           scale, g.N);
-    else
-        hipLaunchKernelGGL(k_density<float>, dim3(blocks), dim3(256), 0, s, (const C2<float>*)phi, (float*)out,
-                           (float)scale, g.N);
     return hipGetLastError();
 }
 

@@ -3,6 +3,8 @@
 
 #include "internal.hpp"
 
+constexpr int kHostScalars = 16;
+
 struct gpe_plan {
     gpe_problem_t prob;
     int dtype = GPE_F64;
@@ -16,6 +18,8 @@ struct gpe_plan {
     gpe::DevBuf scal;              // per-instance solver scalars
     gpe::DevBuf hist;              // per-iteration history rows
     int64_t hist_rows = 0;
+    double* host = nullptr;        // mapped host memory for the scalars a call returns (kHostScalars), and
+    double* host_dev = nullptr;    // its device address: kernels write them there, no copy is queued
     bool f64() const { return dtype == GPE_F64; }
     void release() {
         for (int a = 0; a < 3; ++a) {
@@ -30,5 +34,10 @@ struct gpe_plan {
         solver32.release();
         scal.release();
         hist.release();
+        if (host) {
+            std::lock_guard<std::mutex> lock(gpe::capture_mutex());
+            (void)hipHostFree(host);
+        }
+        host = host_dev = nullptr;
     }
 };

@@ -60,6 +60,7 @@ SIGNATURES = {
     "gpe_plan_create": (_I, [ctypes.POINTER(Problem), _I, ctypes.POINTER(_VP)]),
     "gpe_plan_destroy": (_I, [_VP]),
     "gpe_energy": (_I, [_VP, _VP, _VP, ctypes.POINTER(_D), ctypes.POINTER(_D), _VP]),
+    "gpe_energy_value": (_I, [_VP, _VP, _VP, _VP, ctypes.POINTER(_D), _VP]),
     "gpe_apply_H": (_I, [_VP, _VP, _VP, _VP, _VP]),
     "gpe_apply_H_batched": (_I, [_VP, _I, _VP, _VP, _VP, _VP]),
     "gpe_apply_H_batched_noalloc": (_I, [_VP, _I, _VP, _VP, _VP, _VP]),
@@ -78,6 +79,7 @@ SIGNATURES = {
     "gpe_pcg_solve_nested": (_I, [_I, _I, ctypes.POINTER(Problem), _I, ctypes.POINTER(_VP), ctypes.POINTER(_VP),
                                   ctypes.POINTER(_VP), ctypes.POINTER(PcgOpts), _D, ctypes.POINTER(PcgReport), _VP]),
     "gpe_energy_grad": (_I, [_VP, _VP, _VP, _VP, _VP, ctypes.POINTER(_D), ctypes.POINTER(_D), _VP]),
+    "gpe_energy_grad_scaled": (_I, [_VP, _VP, _VP, _VP, _VP, _VP, _VP, _VP, _VP]),
     "gpe_adjoint_solve": (_I, [_VP, _VP, _VP, _VP, _VP, ctypes.POINTER(PcgOpts), ctypes.POINTER(PcgReport), _VP]),
     "gpe_adjoint_param_grads": (_I, [_VP, _VP, _VP, _VP, ctypes.POINTER(_D), ctypes.POINTER(_D), _VP]),
     "gpe_pcg_profile": (_I, [_VP, _VP, _VP, ctypes.POINTER(PcgOpts), _I, _I, ctypes.POINTER(_D),
@@ -227,6 +229,14 @@ class Plan:
             return E.value, {"kinetic": P[0], "potential": P[1], "interaction": P[2], "rotation": P[3]}
         return E.value
 
+    def energy_value(self, phi, V, stream=None):
+        """gpe_energy_value: the energy as a scalar tensor on the device."""
+        out = torch.empty((), dtype=self.real_dtype, device=phi.device)
+        E = ctypes.c_double()
+        _check(lib().gpe_energy_value(self._h, self._field(phi, "phi"), self._field(V, "V", False),
+                                      ctypes.c_void_p(out.data_ptr()), ctypes.byref(E), _stream(stream)))
+        return out
+
     def apply_H(self, phi, V, out=None, stream=None):
         if out is None:
             out = torch.empty_like(phi)
@@ -295,6 +305,20 @@ class Plan:
                                      self._field(gV, "grad_V", False) if gV is not None else None,
                                      ctypes.byref(db), ctypes.byref(do), _stream(stream)))
         return gphi, gV, db.value, do.value
+
+    def energy_grad_scaled(self, phi, V, gE, stream=None):
+        """gpe_energy_grad_scaled: gE times (grad_phi, grad_V, dE/dbeta, dE/domega), all on the device; gE: a
+        scalar tensor of the plan's real type."""
+        if not gE.is_cuda or gE.dtype != self.real_dtype or gE.numel() != 1:
+            raise TypeError(f"gE must be a {self.real_dtype} device scalar")
+        gphi = torch.empty_like(phi)
+        gV = torch.empty(self.shape, dtype=self.real_dtype, device=phi.device)
+        db, do = (torch.empty((), dtype=self.real_dtype, device=phi.device) for _ in range(2))
+        _check(lib().gpe_energy_grad_scaled(self._h, self._field(phi, "phi"), self._field(V, "V", False),
+                                            ctypes.c_void_p(gE.data_ptr()), self._field(gphi, "grad_phi"),
+                                            self._field(gV, "grad_V", False), ctypes.c_void_p(db.data_ptr()),
+                                            ctypes.c_void_p(do.data_ptr()), _stream(stream)))
+        return gphi, gV, db, do
 
     # -- solver ---------------------------------------------------------------------------------
     def pcg_solve(self, V, phi, stream=None, **opts):
