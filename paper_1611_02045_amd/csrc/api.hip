@@ -72,10 +72,21 @@ void record_tuned_lines(const Geo& g, int AX, int complex_bytes, int B, int C) {
 }
 
 hipError_t build_twiddles(const Geo& g, Twiddles& tw) {
+    std::vector<char> host;
     for (int a = 0; a < g.dim; ++a) {
         const int M = g.n[a];
-        std::vector<double> t64(2 * M);
-        std::vector<float> t32(2 * M);
+        int same = 0;
+        while (same < a && g.n[same] != M) ++same;
+        if (same < a) {
+            tw.off64[a] = tw.off64[same];
+            tw.off32[a] = tw.off32[same];
+            continue;
+        }
+        tw.off64[a] = host.size();
+        tw.off32[a] = tw.off64[a] + sizeof(double) * 2 * M;
+        host.resize(tw.off32[a] + sizeof(float) * 2 * M);
+        double* t64 = (double*)(host.data() + tw.off64[a]);
+        float* t32 = (float*)(host.data() + tw.off32[a]);
         for (int e = 0; e < M; ++e) {
             const double ang = -2.0 * M_PI * (double)e / (double)M;
             t64[2 * e] = std::cos(ang);
@@ -83,31 +94,16 @@ hipError_t build_twiddles(const Geo& g, Twiddles& tw) {
             t32[2 * e] = (float)t64[2 * e];
             t32[2 * e + 1] = (float)t64[2 * e + 1];
         }
-        hipError_t e;
-        if ((e = tw.t64[a].ensure(sizeof(double) * 2 * M)) != hipSuccess) return e;
-        if ((e = tw.t32[a].ensure(sizeof(float) * 2 * M)) != hipSuccess) return e;
-        std::lock_guard<std::mutex> lock(capture_mutex());
-        if ((e = hipMemcpy(tw.t64[a].ptr, t64.data(), sizeof(double) * 2 * M, hipMemcpyHostToDevice)) != hipSuccess)
-            return e;
-        if ((e = hipMemcpy(tw.t32[a].ptr, t32.data(), sizeof(float) * 2 * M, hipMemcpyHostToDevice)) != hipSuccess)
-            return e;
     }
-    return hipSuccess;
+    const hipError_t e = tw.all.ensure(host.size());
+    if (e != hipSuccess) return e;
+    std::lock_guard<std::mutex> lock(capture_mutex());
+    return hipMemcpy(tw.all.ptr, host.data(), host.size(), hipMemcpyHostToDevice);
 }
 
-hipError_t reduce_init(Reduce& r, int instances, int slots, size_t part_doubles) {
-    hipError_t e;
-    if ((e = r.parts.ensure(sizeof(double) * part_doubles)) != hipSuccess) return e;
-    const size_t cbytes = sizeof(unsigned int) * (size_t)instances * slots;
-    if (cbytes > r.counters.bytes) {
-        if ((e = r.counters.ensure(cbytes)) != hipSuccess) return e;
-        std::lock_guard<std::mutex> lock(capture_mutex());
-        if ((e = hipMemset(r.counters.ptr, 0, r.counters.bytes)) != hipSuccess) return e;
-        if ((e = hipDeviceSynchronize()) != hipSuccess) return e;
-    }
-    r.counter_slots = slots;
-    if ((e = r.scalars.ensure(sizeof(double) * 64)) != hipSuccess) return e;
-    return hipSuccess;
+hipError_t reduce_init(Reduce& r, size_t part_doubles, size_t scalar_doubles) {
+    const hipError_t e = r.parts.ensure(sizeof(double) * part_doubles);
+    return e != hipSuccess ? e : r.scalars.ensure(sizeof(double) * scalar_doubles);
 }
 
 __global__ void k_set_scalar(double* dst, double v) {
@@ -173,7 +169,7 @@ int gpe_plan_create(const gpe_problem_t* prob, int dtype, gpe_plan_t** out) {
     p->dtype = dtype;
     p->g = make_geo(*prob);
     hipError_t e = build_twiddles(p->g, p->tw);
-    if (e == hipSuccess) e = reduce_init(p->red, 1, 16, 1 << 18);
+    if (e == hipSuccess) e = reduce_init(p->red, 1 << 18, 128);
     if (e == hipSuccess) e = hipGetDevice(&p->device);
     if (e == hipSuccess) {
         std::lock_guard<std::mutex> lock(capture_mutex());

@@ -81,7 +81,7 @@ int profile_group(ProfileWork& w, int B, const gpe_problem_t* probs, bool in_f64
                   double* bytes, char* names, hipStream_t s) {
     const Geo& g = w.g;
     const int64_t N = g.N;
-    HIPCHK(reduce_init(*w.red, B, R_COUNT, std::max<size_t>(1 << 18, R_COUNT * region_doubles_for(g, B))));
+    HIPCHK(reduce_init(*w.red, std::max<size_t>(1 << 18, R_COUNT * region_doubles_for(g, B)), kVerifyAt + 8 * (size_t)B));
     HIPCHK(w.scal->ensure(3 * sizeof(Scal) * (size_t)B));
     gpe_pcg_opts_t o = opts;
     o.tol_res_inf = 0.0;
@@ -155,7 +155,7 @@ int solve_batch(BatchWork& w, int B, const gpe_problem_t* probs, bool in_f64, co
     const auto t0 = std::chrono::steady_clock::now();
     const Geo& g = w.g;
     const int64_t N = g.N;
-    HIPCHK(reduce_init(*w.red, B, R_COUNT, std::max<size_t>(1 << 18, R_COUNT * region_doubles_for(g, B))));
+    HIPCHK(reduce_init(*w.red, std::max<size_t>(1 << 18, R_COUNT * region_doubles_for(g, B)), kVerifyAt + 8 * (size_t)B));
     HIPCHK(w.scal->ensure(3 * sizeof(Scal) * (size_t)B));
     std::vector<Scal> hs(B);
     for (int b = 0; b < B; ++b) {
@@ -170,14 +170,36 @@ int solve_batch(BatchWork& w, int B, const gpe_problem_t* probs, bool in_f64, co
     const bool mixed = o.precision == 1 && in_f64;
     const size_t cb = in_f64 ? 16 : 8, rb = in_f64 ? 8 : 4;
     std::vector<int64_t> iters32(B, 0);
-    auto verify_b = [&](int b, const void* ph, const void* Vb, double out[3]) -> hipError_t {
-        const Geo gb = instance_geo(g, probs[b]);
+    // Fresh E, lambda and ||r||_inf of the instances listed, from fields and potentials ph[b], Vb[b]: queued one
+    // after another, read back together.  A field verified as the solve left it is not verified again.
+    struct Check {
+        double E, lam, res;
+        bool fresh = false;
+    };
+    std::vector<Check> chk(B);
+    auto verify = [&](const std::vector<int>& which, auto ph, auto Vb) -> hipError_t {
+        if (which.empty()) return hipSuccess;
         hipError_t ee = w.tmp->ensure(2 * cb * (size_t)N);
-        if (ee != hipSuccess) return ee;
-        return in_f64 ? verify_field<double>(gb, *w.tw, ph, Vb, w.tmp->ptr, (char*)w.tmp->ptr + cb * N, probs[b].beta,
-                                             probs[b].omega, *w.red, out, s)
-                      : verify_field<float>(gb, *w.tw, ph, Vb, w.tmp->ptr, (char*)w.tmp->ptr + cb * N, probs[b].beta,
-                                            probs[b].omega, *w.red, out, s);
+        double* const out = (double*)w.red->scalars.ptr + kVerifyAt;
+        for (int b : which) {
+            const Geo gb = instance_geo(g, probs[b]);
+            char* const t = (char*)w.tmp->ptr;
+            if (ee == hipSuccess)
+                ee = in_f64 ? verify_field<double>(gb, *w.tw, ph(b), Vb(b), t, t + cb * N, probs[b].beta, probs[b].omega,
+                                                   *w.red, out + 8 * b, s)
+                            : verify_field<float>(gb, *w.tw, ph(b), Vb(b), t, t + cb * N, probs[b].beta, probs[b].omega,
+                                                  *w.red, out + 8 * b, s);
+        }
+        std::vector<double> h(8 * (size_t)B);
+        if (ee == hipSuccess)
+            ee = hipMemcpyAsync(h.data(), out, sizeof(double) * h.size(), hipMemcpyDeviceToHost, s);
+        if (ee == hipSuccess) ee = hipStreamSynchronize(s);
+        if (ee == hipSuccess)
+            for (int b : which) {
+                const double* r = h.data() + 8 * b;
+                chk[b] = Check{r[4] + r[5] + r[6] + r[7], r[0], r[1], true};
+            }
+        return ee;
     };
     if (!in_f64) {
         IterFields<float> f = carve_fields<float>(*w.f32, (int64_t)B * N, &e);
@@ -231,13 +253,17 @@ int solve_batch(BatchWork& w, int B, const gpe_problem_t* probs, bool in_f64, co
             bool any = false;
             for (int b = 0; b < B; ++b) any = any || !hs[b].done;
             if (!any) break;
+            for (Check& x : chk) x.fresh = false;  // a run renormalises every instance
             if ((st = run<double>(w, B, f, hs, o, s)) != GPE_OK) return st;
             bool again = false;
-            for (int b = 0; b < B; ++b) {
-                if (hs[b].status != ST_OK || hs[b].n >= o.max_iter || o.tol_energy > 0.0) continue;
-                double chk[3];
-                HIPCHK(verify_b(b, f.phi + (int64_t)b * N, f.V + (int64_t)b * N, chk));
-                if (chk[2] > o.tol_res_inf) {
+            std::vector<int> stopped;
+            for (int b = 0; b < B; ++b)
+                if (hs[b].status == ST_OK && hs[b].n < o.max_iter && !(o.tol_energy > 0.0) && !chk[b].fresh)
+                    stopped.push_back(b);
+            HIPCHK(verify(
+                stopped, [&](int b) { return f.phi + (int64_t)b * N; }, [&](int b) { return f.V + (int64_t)b * N; }));
+            for (int b : stopped) {
+                if (chk[b].res > o.tol_res_inf) {
                     hs[b].done = 0;
                     hs[b].tol_res = o.tol_res_inf * (0.9 - 0.1 * attempt);
                     again = true;
@@ -250,22 +276,26 @@ int solve_batch(BatchWork& w, int B, const gpe_problem_t* probs, bool in_f64, co
     const auto t1 = std::chrono::steady_clock::now();
     const double secs = std::chrono::duration<double>(t1 - t0).count();
     int worst = GPE_OK;
+    std::vector<int> rest;
+    for (int b = 0; b < B; ++b)
+        if (!chk[b].fresh) rest.push_back(b);
+    HIPCHK(verify(
+        rest, [&](int b) { return (const void*)phi[b]; }, [&](int b) { return V[b]; }));
+    HIPCHK(hipStreamSynchronize(s));
     for (int b = 0; b < B; ++b) {
-        double chk[3];
-        HIPCHK(verify_b(b, phi[b], V[b], chk));
         gpe_pcg_report_t& r = reports[b];
         std::memset(&r, 0, sizeof(r));
         r.status = status_of(hs[b].status);
         // success means the fresh FP64 residual of the returned state meets the residual tolerance
-        if (r.status == GPE_OK && o.tol_energy == 0.0 && !(chk[2] <= o.tol_res_inf)) r.status = GPE_NOT_CONVERGED;
+        if (r.status == GPE_OK && o.tol_energy == 0.0 && !(chk[b].res <= o.tol_res_inf)) r.status = GPE_NOT_CONVERGED;
         r.switched = mixed ? 1 : 0;
         r.iters = hs[b].n;
         r.iters_fp32 = in_f64 ? (mixed ? iters32[b] : 0) : hs[b].n;
         r.restarts = hs[b].restarts;
         r.halvings = hs[b].halvings;
-        r.E = chk[0];
-        r.lambda = chk[1];
-        r.res_inf = chk[2];
+        r.E = chk[b].E;
+        r.lambda = chk[b].lam;
+        r.res_inf = chk[b].res;
         r.dE = std::fabs(hs[b].E - hs[b].E_prev);
         r.dphi_inf = hs[b].dphi;
         r.seconds = secs;
@@ -291,12 +321,8 @@ int solve_group(int B, const gpe_problem_t* gp, bool in_f64, const void* const* 
         st = GPE_EHIP;
     }
     (void)hipStreamSynchronize(s);
-    for (int a = 0; a < 3; ++a) {
-        tw.t64[a].release();
-        tw.t32[a].release();
-    }
+    tw.release();
     red.parts.release();
-    red.counters.release();
     red.scalars.release();
     scal.release();
     f64.release();
@@ -499,12 +525,8 @@ int gpe_pcg_profile_batched(int count, const gpe_problem_t* probs, int dtype, co
     st = profile_group(w, count, probs, dtype == GPE_F64, V, phi, *opts, iters, cap, avg_ms, bytes, names,
                        (hipStream_t)stream);
     (void)hipStreamSynchronize((hipStream_t)stream);
-    for (int a = 0; a < 3; ++a) {
-        tw.t64[a].release();
-        tw.t32[a].release();
-    }
+    tw.release();
     red.parts.release();
-    red.counters.release();
     red.scalars.release();
     scal.release();
     f64.release();
@@ -586,10 +608,7 @@ int gpe_pcg_solve_nested(int count, int levels, const gpe_problem_t* coarsest, i
         Twiddles tw;
         ~Owned() {
             for (DevBuf& b : bufs) b.release();
-            for (int a = 0; a < 3; ++a) {
-                tw.t64[a].release();
-                tw.t32[a].release();
-            }
+            tw.release();
         }
     } own;
     own.bufs.resize((size_t)levels + 1);  // one field set per coarse level, plus interpolation scratch
@@ -625,11 +644,15 @@ int gpe_pcg_solve_nested(int count, int levels, const gpe_problem_t* coarsest, i
         // interpolate every instance onto the next grid (the solver renormalises its start)
         for (int i = 0; i < count; ++i) {
             const Geo g = make_geo(probs[l][i]);
-            HIPCHK(build_twiddles(g, own.tw));
+            const gpe_problem_t *const p = &probs[l][i], *const q = i > 0 ? &probs[l][i - 1] : nullptr;
+            if (!q || q->dim != p->dim || !std::equal(p->n, p->n + p->dim, q->n)) {
+                HIPCHK(hipStreamSynchronize(s));  // the previous grid's passes read the tables
+                HIPCHK(build_twiddles(g, own.tw));
+            }
             if (g.dim > 1) HIPCHK(own.bufs[levels].ensure(cb * (size_t)g.N * (g.dim == 2 ? 2 : 4)));
             HIPCHK(op_prolong(g, dtype == GPE_F64, own.tw, phis[l][i], phis[l + 1][i], own.bufs[levels].ptr, s));
-            HIPCHK(hipStreamSynchronize(s));  // the tables are rebuilt for the next instance
         }
+        HIPCHK(hipStreamSynchronize(s));
     }
     return worst;
 }

@@ -292,22 +292,4 @@ __device__ __forceinline__ void block_reduce(double (&v)[K], double* red, double
     __syncthreads();
 }
 
-// "Last block done" ticket: every block calls this after writing its partials.  Returns true in
-// exactly one block (the last to arrive), after resetting the counter for the next launch, so
-// the pattern survives graph replays.  All threads of the block get the same answer.
-__device__ __forceinline__ bool last_block(unsigned int* counter, unsigned int nblocks, int* lds_flag) {
-    __threadfence();
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        unsigned int ticket = atomicAdd(counter, 1u);
-        int last = (ticket == nblocks - 1u);
-        if (last) atomicExch(counter, 0u);
-        *lds_flag = last;
-    }
-    __syncthreads();
-    bool last = *lds_flag != 0;
-    if (last) __threadfence();
-    return last;
-}
-
 }  // namespace gpe

@@ -42,24 +42,25 @@ struct DevBuf {
     }
 };
 
-// Twiddle tables exp(-2 pi i e / M), e < M, for each axis, in both precisions.
+// Twiddle tables exp(-2 pi i e / M), e < M, for each axis, in both precisions, in one buffer (one upload);
+// axes of equal length share theirs.
 struct Twiddles {
-    DevBuf t64[3], t32[3];
-    const void* get(int axis, bool f64) const { return f64 ? t64[axis].ptr : t32[axis].ptr; }
+    DevBuf all;
+    size_t off64[3] = {}, off32[3] = {};
+    const void* get(int axis, bool f64) const { return (const char*)all.ptr + (f64 ? off64[axis] : off32[axis]); }
+    void release() { all.release(); }
 };
 
 hipError_t build_twiddles(const Geo& g, Twiddles& tw);
 Geo make_geo(const gpe_problem_t& p);
 
-// Reduction scratch: partial sums (doubles) and per-instance ticket counters (zeroed once).
+// Reduction scratch: partial sums and small device scalars (doubles).
 struct Reduce {
-    DevBuf parts;      // doubles
-    DevBuf counters;   // unsigned ints, one per instance per counter slot
-    DevBuf scalars;    // small device scalars (alpha, energy parts, ...)
-    int counter_slots = 0;
+    DevBuf parts;
+    DevBuf scalars;    // alpha, energy parts, ...
 };
 
-hipError_t reduce_init(Reduce& r, int instances, int slots, size_t part_doubles);
+hipError_t reduce_init(Reduce& r, size_t part_doubles, size_t scalar_doubles = 64);
 
 // ---------------------------------------------------------------------------------------------
 // Operator launchers (ops.hip).  `f64` selects the precision of the fields (complex128/float64

@@ -90,7 +90,6 @@ struct IterCtx {
     Scal* S;
     double* parts;
     size_t region_doubles;
-    unsigned int* counters;
     int precond;
     int pointwise_blocks;
 };

@@ -22,12 +22,8 @@ struct gpe_plan {
     double* host_dev = nullptr;    // its device address: kernels write them there, no copy is queued
     bool f64() const { return dtype == GPE_F64; }
     void release() {
-        for (int a = 0; a < 3; ++a) {
-            tw.t64[a].release();
-            tw.t32[a].release();
-        }
+        tw.release();
         red.parts.release();
-        red.counters.release();
         red.scalars.release();
         tmp.release();
         solver.release();

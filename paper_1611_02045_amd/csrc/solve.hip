@@ -9,6 +9,7 @@
 // Every `refresh_every` iterations L phi and its scalars are recomputed from phi, bounding the
 // drift of the linearity update.  The reported E, lambda and ||r||_inf are recomputed in FP64
 // from the final iterate.
+#include <algorithm>
 #include <chrono>
 #include <cmath>
 #include <cstring>
@@ -275,6 +276,56 @@ struct GraphExec {
     ~GraphExec() { reset(); }
 };
 
+// Copies the states of B instances into mapped host memory (one workgroup each).
+__global__ __launch_bounds__(64) void k_poll(const Scal* S, Scal* host) {
+    static_assert(sizeof(Scal) % sizeof(uint4) == 0, "copied in 16-byte chunks");
+    const uint4* src = reinterpret_cast<const uint4*>(S + blockIdx.x);
+    uint4* dst = reinterpret_cast<uint4*>(host + blockIdx.x);
+    for (int c = threadIdx.x; c < (int)(sizeof(Scal) / sizeof(uint4)); c += 64) dst[c] = src[c];
+}
+
+// Two slots of mapped host memory for the states at the end of a chunk, each with the event that tells
+// when its copy is complete.
+struct PollSlots {
+    int B = 0;
+    Scal *host = nullptr, *dev = nullptr;
+    hipEvent_t ev[2] = {nullptr, nullptr};
+    hipStream_t stream = nullptr;
+    bool used = false;
+    hipError_t init(int count, hipStream_t s) {
+        B = count;
+        stream = s;
+        std::lock_guard<std::mutex> lock(capture_mutex());
+        hipError_t e = hipHostMalloc((void**)&host, 2 * sizeof(Scal) * (size_t)B, hipHostMallocMapped);
+        if (e != hipSuccess) {
+            host = nullptr;
+            return e;
+        }
+        e = hipHostGetDevicePointer((void**)&dev, host, 0);
+        for (int k = 0; k < 2 && e == hipSuccess; ++k) e = hipEventCreateWithFlags(&ev[k], hipEventDisableTiming);
+        return e;
+    }
+    hipError_t queue(const Scal* S, int slot) {
+        used = true;
+        hipLaunchKernelGGL(k_poll, dim3((unsigned)B), dim3(64), 0, stream, S, dev + (size_t)slot * B);
+        const hipError_t e = hipGetLastError();
+        return e != hipSuccess ? e : hipEventRecord(ev[slot], stream);
+    }
+    hipError_t wait(int slot, std::vector<Scal>& out) {
+        const hipError_t e = hipEventSynchronize(ev[slot]);
+        if (e == hipSuccess) std::copy(host + (size_t)slot * B, host + (size_t)(slot + 1) * B, out.begin());
+        return e;
+    }
+    // queued kernels may still write the slots (and use what its owner frees after it)
+    ~PollSlots() {
+        if (used) (void)hipStreamSynchronize(stream);
+        std::lock_guard<std::mutex> lock(capture_mutex());
+        for (hipEvent_t x : ev)
+            if (x) (void)hipEventDestroy(x);
+        if (host) (void)hipHostFree(host);
+    }
+};
+
 template <typename T>
 hipError_t run_phase(PhaseArgs& pa, IterFields<T> f, std::vector<Scal>& host_S, hipStream_t s_caller) {
     const Geo& g = pa.g;
@@ -321,7 +372,6 @@ hipError_t run_phase(PhaseArgs& pa, IterFields<T> f, std::vector<Scal>& host_S, 
     c.S = pa.S;
     c.parts = (double*)pa.red->parts.ptr;
     c.region_doubles = pa.region_doubles;
-    c.counters = (unsigned int*)pa.red->counters.ptr;
     c.precond = pa.precond;
     c.pointwise_blocks = (int)std::max<int64_t>(1, std::min<int64_t>(1024, N / 1024));
     int64_t since_refresh = 0;
@@ -329,68 +379,27 @@ hipError_t run_phase(PhaseArgs& pa, IterFields<T> f, std::vector<Scal>& host_S, 
     int64_t max_iter = 0;
     for (int b = 0; b < B; ++b) max_iter = std::max<int64_t>(max_iter, host_S[b].max_iter);
     // A chunk of check_every iterations launches the same kernels with the same arguments every
-    // time (the r / r_{n-1} roles swap each iteration, so an even chunk ends where it started): after
-    // one chunk ran eagerly, the next is captured into a graph and every later chunk replays it.
+    // time (the r / r_{n-1} roles swap each iteration, so an even chunk ends where it started): the
+    // first chunk runs eagerly, is captured into a graph while the device works on it, and every later
+    // chunk replays that.
     GraphExec graph;
-    int64_t chunks = 0;
     // device list of the unfinished instances (used when they are not contiguous), owned by the phase
     struct OwnedBuf : DevBuf {
         ~OwnedBuf() { release(); }
     } imap;
     std::vector<int> imap_host;
     if ((e = imap.ensure(sizeof(int) * (size_t)B)) != hipSuccess) return e;
-    for (;;) {
+    // The host polls one chunk behind: while it waits for a chunk's states the next chunk is already
+    // queued, so the device does not wait for the poll and the launch (65 us a chunk, against 600 us of
+    // work on 256^2).  The chunk after the one that finishes every instance is queued in vain: its
+    // kernels return at once.  A chunk's states reach one of two slots of mapped host memory.
+    PollSlots poll;
+    if ((e = poll.init(B, s)) != hipSuccess) return e;
+    int64_t head = 0, tail = 0;  // chunks queued, chunks polled
+    auto queue_chunk = [&]() -> hipError_t {
         // host-side guard: every queued iteration either advances n or finishes the instance
         if (queued > 2 * max_iter + 4 * (int64_t)pa.check_every + 64) return hipErrorUnknown;
-        queued += pa.check_every;
-        if (!graph.exec && want_graph && chunks >= 1) {
-            if ((e = graph.capture(s, [&] { return enqueue_iterations<T>(c, pa.check_every, s); })) != hipSuccess)
-                return e;
-        }
-        if (graph.exec) {
-            if ((e = graph.launch(s)) != hipSuccess) return e;
-        } else {
-            if ((e = enqueue_iterations<T>(c, pa.check_every, s)) != hipSuccess) return e;
-        }
-        ++chunks;
-        since_refresh += pa.check_every;
-        if ((e = hipMemcpyAsync(host_S.data(), S_dir, sizeof(Scal) * B, hipMemcpyDeviceToHost, s)) != hipSuccess)
-            return e;
-        if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-        bool all_done = true;
-        for (int b = 0; b < B; ++b) all_done = all_done && host_S[b].done;
-        if (all_done) break;
-        // Converged instances are left out of later launches (a masked instance still costs its
-        // workgroups' state and row reads in every pass): a contiguous run of unfinished instances is
-        // launched as a range, any other set through the device list of their indices.  Tiles and row
-        // layout keep following all B instances.  The stream is idle here, so the list can be
-        // rewritten and the graph holding the old launches can go; the next chunk captures anew.
-        {
-            std::vector<int> run;
-            for (int b = 0; b < B; ++b)
-                if (!host_S[b].done) run.push_back(b);
-            const int nl = (int)run.size();
-            const bool contiguous = run.back() - run.front() + 1 == nl;
-            const bool same = contiguous ? (!c.g.imap && c.g.b0 == run.front() && (c.g.bl > 0 ? c.g.bl : B) == nl)
-                                         : (c.g.imap && c.g.bl == nl && run == imap_host);
-            if (!same) {
-                if (contiguous) {
-                    c.g.imap = nullptr;
-                    c.g.b0 = run.front();
-                } else {
-                    imap_host = run;
-                    if ((e = hipMemcpyAsync(imap.ptr, imap_host.data(), sizeof(int) * nl, hipMemcpyHostToDevice, s)) !=
-                        hipSuccess)
-                        return e;
-                    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-                    c.g.imap = (const int*)imap.ptr;
-                    c.g.b0 = 0;
-                }
-                c.g.bl = nl;
-                graph.reset();
-            }
-        }
-        // Every queued iteration of an unfinished instance ran, so r/rp roles are in sync.
+        hipError_t ee;
         if (pa.refresh_every > 0 && since_refresh >= pa.refresh_every) {
             since_refresh = 0;
             for (int b = 0; b < B; ++b) {
@@ -402,12 +411,67 @@ hipError_t run_phase(PhaseArgs& pa, IterFields<T> f, std::vector<Scal>& host_S, 
                     gb.dk[a] = host_S[b].dk[a];
                 }
                 gb.cell = host_S[b].cell;
-                if ((e = refresh_instance<T>(gb, *pa.tw, c.f, (int64_t)b * N, S_dir + b, host_S[b].beta,
-                                             host_S[b].omega, *pa.red, false, s)) != hipSuccess)
-                    return e;
+                if ((ee = refresh_instance<T>(gb, *pa.tw, c.f, (int64_t)b * N, S_dir + b, host_S[b].beta,
+                                              host_S[b].omega, *pa.red, false, s)) != hipSuccess)
+                    return ee;
             }
         }
+        ee = graph.exec ? graph.launch(s) : enqueue_iterations<T>(c, pa.check_every, s);
+        if (ee != hipSuccess) return ee;
+        queued += pa.check_every;
+        since_refresh += pa.check_every;
+        if ((ee = poll.queue(S_dir, (int)(head & 1))) != hipSuccess) return ee;
+        ++head;
+        if (!graph.exec && want_graph && queued <= max_iter)
+            ee = graph.capture(s, [&] { return enqueue_iterations<T>(c, pa.check_every, s); });
+        return ee;
+    };
+    for (;;) {
+        if (head == tail && (e = queue_chunk()) != hipSuccess) return e;
+        if (head - tail < 2 && queued <= max_iter && (e = queue_chunk()) != hipSuccess) return e;
+        if ((e = poll.wait((int)(tail & 1), host_S)) != hipSuccess) return e;
+        ++tail;
+        std::vector<int> run;
+        for (int b = 0; b < B; ++b)
+            if (!host_S[b].done) run.push_back(b);
+        if (run.empty()) break;
+        // Converged instances are left out of later launches (a masked instance still costs its
+        // workgroups' state and row reads in every pass): a contiguous run of unfinished instances is
+        // launched as a range, any other set through the device list of their indices.  Tiles and row
+        // layout keep following all B instances.  The chunk in flight still holds the old launches: it
+        // is waited for before the list is rewritten and the graph goes.
+        auto launched = [&] {
+            const int nl = (int)run.size();
+            return run.back() - run.front() + 1 == nl
+                       ? (!c.g.imap && c.g.b0 == run.front() && (c.g.bl > 0 ? c.g.bl : B) == nl)
+                       : (c.g.imap && c.g.bl == nl && run == imap_host);
+        };
+        if (launched()) continue;
+        if (head > tail) {
+            if ((e = poll.wait((int)(tail & 1), host_S)) != hipSuccess) return e;
+            ++tail;
+            run.clear();
+            for (int b = 0; b < B; ++b)
+                if (!host_S[b].done) run.push_back(b);
+            if (run.empty()) break;
+        }
+        if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
+        const int nl = (int)run.size();
+        if (run.back() - run.front() + 1 == nl) {
+            c.g.imap = nullptr;
+            c.g.b0 = run.front();
+        } else {
+            imap_host = run;
+            if ((e = hipMemcpyAsync(imap.ptr, imap_host.data(), sizeof(int) * nl, hipMemcpyHostToDevice, s)) != hipSuccess)
+                return e;
+            if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
+            c.g.imap = (const int*)imap.ptr;
+            c.g.b0 = 0;
+        }
+        c.g.bl = nl;
+        graph.reset();
     }
+    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;  // the chunk queued in vain
     pa.final_f_r_is_rp = false;
     return hipSuccess;
 }
@@ -440,7 +504,6 @@ hipError_t profile_phase(PhaseArgs& pa, IterFields<T> f, std::vector<Scal>& host
     c.S = pa.S;
     c.parts = (double*)pa.red->parts.ptr;
     c.region_doubles = pa.region_doubles;
-    c.counters = (unsigned int*)pa.red->counters.ptr;
     c.precond = pa.precond;
     c.pointwise_blocks = (int)std::max<int64_t>(1, std::min<int64_t>(1024, N / 1024));
     c.timer = &timer;
@@ -459,29 +522,21 @@ template hipError_t profile_phase<float>(PhaseArgs&, IterFields<float>, std::vec
 template hipError_t run_phase<double>(PhaseArgs&, IterFields<double>, std::vector<Scal>&, hipStream_t);
 template hipError_t run_phase<float>(PhaseArgs&, IterFields<float>, std::vector<Scal>&, hipStream_t);
 
-// Fresh FP64 (or FP32 plan) energy, lambda and residual of one field.
+// Fresh FP64 (or FP32 plan) energy parts, lambda and residual of one field, queued into out.
 template <typename T>
 hipError_t verify_field(const Geo& g, const Twiddles& tw, const void* phi, const void* V, void* hphi, void* tmp,
-                        double beta, double omega, Reduce& red, double out[3], hipStream_t s) {
+                        double beta, double omega, Reduce& red, double* out, hipStream_t s) {
     const bool f64 = sizeof(T) == 8;
     hipError_t e;
     if ((e = op_apply(g, f64, 1, tw, phi, V, hphi, tmp, beta, omega, true, s)) != hipSuccess) return e;
-    double* sc = (double*)red.scalars.ptr;
     double* parts = (double*)red.parts.ptr;
     const int nb = 256;
     hipLaunchKernelGGL(k_verify_dot<T>, dim3(nb), dim3(256), 0, s, (const C2<T>*)phi, (const C2<T>*)hphi, g.N, parts);
     hipLaunchKernelGGL(k_verify_res<T>, dim3(nb), dim3(256), 0, s, (const C2<T>*)phi, (const C2<T>*)hphi, g.N, parts, nb,
-                       parts + 2 * nb, sc + 32);
-    hipLaunchKernelGGL(k_max_collect, dim3(1), dim3(256), 0, s, parts + 2 * nb, nb, sc + 33);
+                       parts + 2 * nb, out);
+    hipLaunchKernelGGL(k_max_collect, dim3(1), dim3(256), 0, s, parts + 2 * nb, nb, out + 1);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    if ((e = op_energy(g, f64, tw, phi, V, beta, omega, red, sc + 36, s)) != hipSuccess) return e;
-    double h[8];
-    if ((e = hipMemcpyAsync(h, sc + 32, sizeof(h), hipMemcpyDeviceToHost, s)) != hipSuccess) return e;
-    if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;
-    out[0] = h[4] + h[5] + h[6] + h[7];  // E
-    out[1] = h[0];                        // lambda
-    out[2] = h[1];                        // ||r||_inf
-    return hipSuccess;
+    return op_energy(g, f64, tw, phi, V, beta, omega, red, out + 4, s);
 }
 
 template hipError_t verify_field<double>(const Geo&, const Twiddles&, const void*, const void*, void*, void*, double,

@@ -28,9 +28,11 @@ template <typename T>
 hipError_t profile_phase(PhaseArgs& pa, IterFields<T> f, std::vector<Scal>& host_S, int iters, KernelTimer& timer,
                          hipStream_t s);
 
+// Queues the fresh FP64 check of one field: out (device, 8 doubles) <- {lambda, ||r||_inf, -, -, energy parts}.
 template <typename T>
 hipError_t verify_field(const Geo& g, const Twiddles& tw, const void* phi, const void* V, void* hphi, void* tmp,
-                        double beta, double omega, Reduce& red, double out[3], hipStream_t s);
+                        double beta, double omega, Reduce& red, double* out, hipStream_t s);
+constexpr size_t kVerifyAt = 64;  // the checks' results in Reduce::scalars, 8 per instance
 
 template <typename T>
 IterFields<T> carve_fields(DevBuf& buf, int64_t BN, hipError_t* err);
