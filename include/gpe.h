@@ -227,13 +227,14 @@ int gpe_pcg_solve(gpe_plan_t* plan, const void* V, void* phi_inout, const gpe_pc
 int gpe_pcg_history(gpe_plan_t* plan, double* hist, int cap);
 
 /* Independent solves of `count` problems (possibly different grids, beta, omega, L); instances
- * of equal grid share each kernel launch and converged instances leave the launches.  The instances
- * of a grid are split into two parts, and the parts of all grids are solved concurrently, each
+ * of equal grid share each kernel launch and converged instances leave the launches.  The grids, or two
+ * halves of a large batch of one grid, are solved concurrently, each
  * on its own stream (the caller's for the first, default-priority streams the call creates for
  * the others) driven by its own host thread; the created streams first wait for the work already
- * queued on the caller's stream.  Results do not depend on the split.  V[i], phi_inout[i]: device fields of instance i in its own layout and
+ * queued on the caller's stream.  The split changes results by rounding at most (tiles follow the
+ * number of instances that share a launch).  V[i], phi_inout[i]: device fields of instance i in its own layout and
  * in the type `dtype`.  reports: host array of `count`.  Returns the worst status.
- * Synchronises both streams before returning. */
+ * Synchronises every stream it used before returning. */
 int gpe_pcg_solve_batched(int count, const gpe_problem_t* probs, int dtype, void* const* V,
                           void* const* phi_inout, const gpe_pcg_opts_t* opts,
                           gpe_pcg_report_t* reports, void* stream);

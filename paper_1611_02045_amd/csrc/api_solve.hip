@@ -43,6 +43,7 @@ struct BatchWork {
     DevBuf* f64;           // FP64 fields (B instances)
     DevBuf* f32;           // FP32 fields (B instances)
     DevBuf* tmp;           // verification scratch (2 fields of one instance)
+    bool own_stream = false;  // the stream is a non-blocking one of this library's (graphs are captured on it)
 };
 
 template <typename T>
@@ -58,6 +59,7 @@ int run(BatchWork& w, int B, IterFields<T> f, std::vector<Scal>& hs, const gpe_p
     pa.check_every = o.check_every;
     pa.refresh_every = o.refresh_every;
     pa.use_graph = o.use_graph != 0;
+    pa.own_stream = w.own_stream;
     pa.final_f_r_is_rp = false;
     HIPCHK(run_phase<T>(pa, f, hs, s));
     return GPE_OK;
@@ -306,7 +308,7 @@ int solve_batch(BatchWork& w, int B, const gpe_problem_t* probs, bool in_f64, co
 
 // One grid group on one stream: twiddles, workspace, the solve, release.
 int solve_group(int B, const gpe_problem_t* gp, bool in_f64, const void* const* gV, void* const* gphi,
-                const gpe_pcg_opts_t& o, gpe_pcg_report_t* rep, hipStream_t s) {
+                const gpe_pcg_opts_t& o, gpe_pcg_report_t* rep, hipStream_t s, bool own_stream) {
     Geo g = make_geo(gp[0]);
     Twiddles tw;
     Reduce red;
@@ -314,7 +316,7 @@ int solve_group(int B, const gpe_problem_t* gp, bool in_f64, const void* const* 
     int st;
     hipError_t e = build_twiddles(g, tw);
     if (e == hipSuccess) {
-        BatchWork w{g, &tw, &red, &scal, &f64, &f32, &tmp};
+        BatchWork w{g, &tw, &red, &scal, &f64, &f32, &tmp, own_stream};
         st = solve_batch(w, B, gp, in_f64, gV, gphi, o, nullptr, 0, rep, s);
     } else {
         set_error(std::string("twiddle tables: ") + hipGetErrorString(e));
@@ -400,22 +402,30 @@ int run_concurrent(int n, hipStream_t s, F task) {
     return worst;
 }
 
-// Instances of one grid solved as kSolveStreams independent parts, each on its own stream driven by
-// its own host thread.  A part's kernels then run while another part's are in a different phase
-// (one loading fields, the other transforming), which a single batched launch cannot do: every
-// workgroup of a launch passes through the same phases at the same time.  Each instance's
-// arithmetic does not depend on how the instances are grouped, so results are bit-identical to a
-// single batch.  Measured on the eight-start 512^2 step: one batch 1.14 s (mixed) / 3.01 s (FP64),
-// two parts 0.97 / 2.45 s, four 0.98 / 2.50 s, eight 1.11 / 2.72 s.
-constexpr int kSolveStreams = 2;
+// Instances of one grid solved as independent parts, each on its own stream driven by its own host thread.
+// A part's kernels then run while another part's are in a different phase (one loading fields, the other
+// transforming), which a single batched launch cannot do: every workgroup of a launch passes through the
+// same phases at the same time.  That pays only where a part's launches still
+// fill the chip: kernels of several streams share it but barely overlap in time while they leave it idle
+// (three grid groups that take 17.5, 10.2 and 7.0 ms alone took 34.7 ms side by side as six parts, 21.1 as
+// three).  Hence two parts for a call of one grid whose halves give every CU two workgroups, else one.
+// Per iteration, one batch against two parts (us): 8 x 512^2 FP64 192, 161; 16 x 512^2 FP32 185, 166;
+// 16 x 256^2 FP64 104, 96; 8 x 512^2 FP32 104, 107; 4 x 512^2 FP64 102, 98 (with the second part's set-up a
+// solve to 1e-8 takes 16.2 ms whole, 18.0 in parts).
+int solve_parts(int B, const gpe_problem_t& p, bool f32_fields, int groups) {
+    if (B < 2 || groups > 1 || p.dim < 2) return 1;
+    const Geo g = make_geo(p);
+    const int64_t half = (int64_t)pass_blocks_per_field(g, 0, f32_fields ? 8 : 16, B / 2, true) * (B / 2);
+    return half >= 2 * device_cus() ? 2 : 1;
+}
 
-int solve_group_split(int B, const gpe_problem_t* gp, bool in_f64, const void* const* gV, void* const* gphi,
-                      const gpe_pcg_opts_t& o, gpe_pcg_report_t* rep, hipStream_t s) {
-    const int P = std::min(B, kSolveStreams);
+int solve_group_split(int P, int B, const gpe_problem_t* gp, bool in_f64, const void* const* gV, void* const* gphi,
+                      const gpe_pcg_opts_t& o, gpe_pcg_report_t* rep, hipStream_t s, bool own_stream) {
     std::vector<int> b0(P + 1);
     for (int k = 0; k <= P; ++k) b0[k] = (int)((int64_t)B * k / P);
     return run_concurrent(P, s, [&](int k, hipStream_t sk) {
-        return solve_group(b0[k + 1] - b0[k], gp + b0[k], in_f64, gV + b0[k], gphi + b0[k], o, rep + b0[k], sk);
+        return solve_group(b0[k + 1] - b0[k], gp + b0[k], in_f64, gV + b0[k], gphi + b0[k], o, rep + b0[k], sk,
+                           own_stream || k > 0);
     });
 }
 
@@ -573,8 +583,9 @@ int gpe_pcg_solve_batched(int count, const gpe_problem_t* probs, int dtype, void
     const gpe_pcg_opts_t& o = *opts;
     const int worst = run_concurrent(G, s, [&](int g, hipStream_t sg) {
         const size_t a = first[g];
-        return solve_group_split((int)(first[g + 1] - a), gp.data() + a, in_f64, gV.data() + a, gphi.data() + a,
-                                 o, rep.data() + a, sg);
+        const int Bg = (int)(first[g + 1] - a);
+        return solve_group_split(solve_parts(Bg, gp[a], !in_f64 || o.precision == 1, G), Bg, gp.data() + a, in_f64,
+                                 gV.data() + a, gphi.data() + a, o, rep.data() + a, sg, g > 0);
     });
     if (worst == GPE_EHIP || worst == GPE_EINVAL) return worst;
     for (int i = 0; i < count; ++i) reports[order[i]] = rep[i];

@@ -333,13 +333,14 @@ hipError_t run_phase(PhaseArgs& pa, IterFields<T> f, std::vector<Scal>& host_S, 
     const int64_t N = g.N;
     hipError_t e;
     // Graph capture is not possible on the legacy default stream (the usual caller's stream): with
-    // graphs the phase runs on a private stream that first waits for the caller's queued work; the
-    // loop below ends with a synchronisation of that stream, so nothing is left queued on it.
+    // graphs the phase runs on a private stream that first waits for the caller's queued work (or on the
+    // stream of a batch's part as it is); the loop below ends with a synchronisation of that stream, so
+    // nothing is left queued on it.
     // (1-D: a chunk is one launch, with nothing to capture)
     const bool want_graph = pa.use_graph && pa.check_every % 2 == 0 && g.dim > 1;
     PrivateStream own;
     hipStream_t s = s_caller;
-    if (want_graph) {
+    if (want_graph && !pa.own_stream) {
         if ((e = own.create_after(s_caller)) != hipSuccess) return e;
         s = own.s;
     }

@@ -17,6 +17,7 @@ struct PhaseArgs {
     int precond;
     int check_every;
     int refresh_every;
+    bool own_stream = false; // the phase's stream may be captured (a non-blocking one of this library's)
     bool use_graph = false;  // replay chunks of check_every iterations as a captured graph
     bool final_f_r_is_rp;
 };
