@@ -84,7 +84,7 @@ int profile_group(ProfileWork& w, int B, const gpe_problem_t* probs, bool in_f64
     const Geo& g = w.g;
     const int64_t N = g.N;
     HIPCHK(reduce_init(*w.red, std::max<size_t>(1 << 18, R_COUNT * region_doubles_for(g, B)), kVerifyAt + 8 * (size_t)B));
-    HIPCHK(w.scal->ensure(3 * sizeof(Scal) * (size_t)B));
+    HIPCHK(w.scal->ensure(2 * sizeof(Scal) * (size_t)B));
     gpe_pcg_opts_t o = opts;
     o.tol_res_inf = 0.0;
     o.tol_energy = 0.0;
@@ -158,7 +158,7 @@ int solve_batch(BatchWork& w, int B, const gpe_problem_t* probs, bool in_f64, co
     const Geo& g = w.g;
     const int64_t N = g.N;
     HIPCHK(reduce_init(*w.red, std::max<size_t>(1 << 18, R_COUNT * region_doubles_for(g, B)), kVerifyAt + 8 * (size_t)B));
-    HIPCHK(w.scal->ensure(3 * sizeof(Scal) * (size_t)B));
+    HIPCHK(w.scal->ensure(2 * sizeof(Scal) * (size_t)B));
     std::vector<Scal> hs(B);
     for (int b = 0; b < B; ++b) {
         hs[b] = make_scal(probs[b], instance_geo(g, probs[b]), o);

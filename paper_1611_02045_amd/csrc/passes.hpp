@@ -226,6 +226,19 @@ struct PrefetchEarly<Op, std::void_t<decltype(Op::PREFETCH_EARLY)>> {
     static constexpr bool value = Op::PREFETCH_EARLY;
 };
 
+// Entries per partial row and the first that the Op writes (Op::ROW, Op::ROW_AT; default: its K sums are
+// the row).  The others are zeros (ROW_FILL), or another pass's over the same tiles.
+template <class Op, class = void>
+struct RowShape {
+    static constexpr int width = Op::K, at = 0;
+    static constexpr bool fill = false;
+};
+template <class Op>
+struct RowShape<Op, std::void_t<decltype(Op::ROW)>> {
+    static constexpr int width = Op::ROW, at = Op::ROW_AT;
+    static constexpr bool fill = Op::ROW_FILL && width > Op::K;
+};
+
 // Twiddles per thread fetched into registers ahead of the scalar logic (more go straight to LDS).
 constexpr int kTwiddleRegs = 4;  // tw0..tw3 in pass_kernel
 
@@ -337,7 +350,13 @@ void pass_kernel(Geo g, int C, const C2<T>* __restrict__ twg, Op op, Partials pr
     op.store(g, lc, st, v, acc);
 
     if constexpr (Op::K > 0) {
-        double* P = pr.parts + ((size_t)lc.b * pr.row_stride() + pr.off + blk_in_inst) * Op::K;
+        using Row = RowShape<Op>;
+        double* R = pr.parts + ((size_t)lc.b * pr.row_stride() + pr.off + blk_in_inst) * Row::width;
+        if constexpr (Row::fill) {
+            for (int k = threadIdx.x; k < Row::width; k += blockDim.x)
+                if (k < Row::at || k >= Row::at + Op::K) R[k] = 0.0;
+        }
+        double* P = R + Row::at;
         block_reduce_to<Op::K, Op::MAXMASK>(acc, red, [P](int k, double s) { P[k] = s; });
     }
 }

@@ -59,15 +59,10 @@ hipError_t enqueue_iteration(const IterCtx<T>& c, hipStream_t s) {
     const int cb = (int)sizeof(C2<T>);
     const IterFields<T>& f = c.f;
     Scal* S_step = c.S;
-    Scal* S_res = c.S + c.B;
-    Scal* S_dir = c.S + 2 * c.B;
+    Scal* S_dir = c.S + c.B;
     // launched instances: [g.b0, g.b0 + Bl), or g.imap[0 .. Bl) (converged instances are not launched)
     const int Bl = g.bl > 0 ? g.bl : c.B;
     hipError_t e;
-    auto region = [&](int r, int ax) {
-        const int nb = pass_blocks_per_field(g, ax, cb, c.B, true);
-        return Partials{c.parts + (size_t)r * c.region_doubles, nb, nb, 0};
-    };
     // the view a consumer absorbs: the region itself, or its collapse into a row per kCollapseRows
     auto consumable = [&](const Partials& p, int rc, int K) -> Partials {
         double* const to = c.parts + (size_t)rc * c.region_doubles;
@@ -98,70 +93,57 @@ hipError_t enqueue_iteration(const IterCtx<T>& c, hipStream_t s) {
     if (c.precond == GPE_P_COMBINED) pre = post = 1;
     if (c.precond == GPE_P_C1) post = 2;
     if (c.precond == GPE_P_C2 || c.precond == GPE_P_POTENTIAL) pre = 2;
-    Partials pres = none, pdir;
-    const Scal* dir_in;
+    Partials pa;  // the phase-A rows
     if (!spectral_p) {
         // diagonal P (identity or P_V): one pointwise kernel for residual, P r and every sum
         const int nbpi = c.pointwise_blocks;
-        const Partials pr{c.parts + (size_t)R_A1 * c.region_doubles, nbpi, nbpi, 0};
+        pa = Partials{c.parts + (size_t)R_A * c.region_doubles, nbpi, nbpi, 0};
         launch_timed(tick("step_resid_diag", 21), k_resid_diag<T>, dim3((unsigned)(nbpi * Bl)), dim3(256), 0, s, f,
-                     S_dir, S_step, g.N, nbpi, pre, sb, pr, g.b0, g.imap);
+                     S_dir, S_step, g.N, nbpi, pre, sb, pa, g.b0, g.imap);
         if ((e = hipGetLastError()) != hipSuccess) return e;
-        pres = consumable(pr, R_A1C, A_K);
-        pdir = pres;
-        dir_in = S_step;
     } else {
+        pa = Partials{c.parts + (size_t)R_A * c.region_doubles, nbx, nbx, 0};
         OpResid<T> op{f, S_dir, S_step, sb, pre};
-        const Partials pa1r = region(R_A1, 0);
-        if ((e = launch_pass<T, 0>(g, c.B, c.tw->get(0, f64), op, pa1r, s,
-                tick("step_resid_fwd_x", 17))) != hipSuccess)
+        if ((e = launch_pass<T, 0>(g, c.B, c.tw->get(0, f64), op, pa, s, tick("step_resid_fwd_x", 17))) != hipSuccess)
             return e;
-        const Partials pa1 = consumable(pa1r, R_A1C, A_K);
         if (g.dim == 2) {
-            OpPMid<T, 1, true, true, true> y{f.w, S_step, S_res, pa1};
-            if ((e = launch_pass<T, 1>(g, c.B, c.tw->get(1, f64), y, none, s,
-                    tick("resid_test_precond_y", 4))) != hipSuccess)
+            OpPMid<T, 1, true, true> y{f.w, S_step};
+            if ((e = launch_pass<T, 1>(g, c.B, c.tw->get(1, f64), y, none, s, tick("precond_y", 4))) != hipSuccess)
                 return e;
         } else {
-            OpPMid<T, 1, true, false, true> y1{f.w, S_step, S_res, pa1};
-            if ((e = launch_pass<T, 1>(g, c.B, c.tw->get(1, f64), y1, none, s,
-                    tick("resid_test_precond_fwd_y", 4))) != hipSuccess)
+            OpPMid<T, 1, true, false> y1{f.w, S_step};
+            if ((e = launch_pass<T, 1>(g, c.B, c.tw->get(1, f64), y1, none, s, tick("precond_fwd_y", 4))) != hipSuccess)
                 return e;
-            OpPMid<T, 2, true, true, false> z{f.w, S_res, nullptr, none};
-            if ((e = launch_pass<T, 2>(g, c.B, c.tw->get(2, f64), z, none, s,
-                    tick("precond_z", 4))) != hipSuccess)
+            OpPMid<T, 2, true, true> z{f.w, S_step};
+            if ((e = launch_pass<T, 2>(g, c.B, c.tw->get(2, f64), z, none, s, tick("precond_z", 4))) != hipSuccess)
                 return e;
-            OpPMid<T, 1, false, true, false> y2{f.w, S_res, nullptr, none};
-            if ((e = launch_pass<T, 1>(g, c.B, c.tw->get(1, f64), y2, none, s,
-                    tick("precond_inv_y", 4))) != hipSuccess)
+            OpPMid<T, 1, false, true> y2{f.w, S_step};
+            if ((e = launch_pass<T, 1>(g, c.B, c.tw->get(1, f64), y2, none, s, tick("precond_inv_y", 4))) != hipSuccess)
                 return e;
         }
-        OpPLast<T> op3{f, S_res, post};
-        const Partials pa3 = region(R_A3, 0);
-        if ((e = launch_pass<T, 0>(g, c.B, c.tw->get(0, f64), op3, pa3, s,
-                tick("precond_inv_x", 13))) != hipSuccess)
+        OpPLast<T> op3{f, S_step, post};
+        if ((e = launch_pass<T, 0>(g, c.B, c.tw->get(0, f64), op3, pa, s, tick("precond_inv_x", 13))) != hipSuccess)
             return e;
-        pdir = consumable(pa3, R_A3C, A_K);
-        dir_in = S_res;
     }
+    const Partials pdir = consumable(pa, R_AC, A_K);
     // ---- phase B ----
     if (g.dim == 2) {
-        OpLp<T, 0, true, false> ox{f, dir_in, S_dir, pres, pdir};
+        OpLp<T, 0, true, false> ox{f, S_step, S_dir, pdir};
         if ((e = launch_pass<T, 0>(g, c.B, c.tw->get(0, f64), ox, pb0, s,
-                tick("dir_Lp_x", 11))) != hipSuccess)
+                tick("test_dir_Lp_x", 11))) != hipSuccess)
             return e;
-        OpLp<T, 1, false, true> oy{f, S_dir, nullptr, none, none};
+        OpLp<T, 1, false, true> oy{f, S_dir, nullptr, none};
         if ((e = launch_pass<T, 1>(g, c.B, c.tw->get(1, f64), oy, pb1, s,
                 tick("Lp_y_linesearch", 8))) != hipSuccess)
             return e;
     } else {
-        OpLp<T, 0, true, false> ox{f, dir_in, S_dir, pres, pdir};
+        OpLp<T, 0, true, false> ox{f, S_step, S_dir, pdir};
         if ((e = launch_pass<T, 0>(g, c.B, c.tw->get(0, f64), ox, pb0, s,
-                tick("dir_Lp_x", 11))) != hipSuccess)
+                tick("test_dir_Lp_x", 11))) != hipSuccess)
             return e;
-        OpLp<T, 1, false, false> oy{f, S_dir, nullptr, none, none};
+        OpLp<T, 1, false, false> oy{f, S_dir, nullptr, none};
         if ((e = launch_pass<T, 1>(g, c.B, c.tw->get(1, f64), oy, pb1, s, tick("Lp_y", 8))) != hipSuccess) return e;
-        OpLp<T, 2, false, true> oz{f, S_dir, nullptr, none, none};
+        OpLp<T, 2, false, true> oz{f, S_dir, nullptr, none};
         if ((e = launch_pass<T, 2>(g, c.B, c.tw->get(2, f64), oz, pb2, s,
                 tick("Lp_z_linesearch", 8))) != hipSuccess)
             return e;

@@ -23,7 +23,7 @@ struct IterFields {
 // Partial-sum regions of the reducing passes, and their collapsed counterparts (a row per
 // 64 rows) used when a pass has more workgroups per instance than a consumer should re-reduce.
 enum : int {
-    R_A1 = 0, R_A3, R_B, R_A1C = R_B + 3, R_A3C, R_BC, R_COUNT  // R_B spans three regions (x, y, z passes)
+    R_A = 0, R_B, R_AC = R_B + 3, R_BC, R_COUNT  // R_B spans three regions (x, y, z passes)
 };
 
 // Optional per-kernel timing of an iteration (gpe_pcg_profile): every launch of the iteration
@@ -94,22 +94,27 @@ struct IterCtx {
     int pointwise_blocks;
 };
 
-// Phase A sums: residual maximum, non-finite flag, the inner products of the CG update, and the
-// fresh scalars of the (just updated) iterate: <phi, L phi>, sum|phi|^4, ||phi||^2,
-// ||phi_n - phi_{n-1}||_inf.
+// Phase A sums.  The first pass (the residual's) forms the first kResidSums: residual maximum, non-finite
+// flag, ||phi_n - phi_{n-1}||_inf, and the fresh scalars of the (just updated) iterate <phi, L phi>,
+// sum|phi|^4, ||phi||^2; the last pass the inner products of the CG update.  Both run over the same x
+// lines in the same tiles, so each fills its own entries of one row per workgroup, and the direction
+// pass absorbs both at once.
 enum : int {
-    A_RES = 0, A_NF, A_RPR, A_RPPR, A_PRPHI, A_PRPR, A_PRPP, A_RPP, A_PPPHI, A_PPPP, A_RPHI, A_PHIPHI,
-    A_A, A_Q4, A_N2, A_DPHI, A_K = 16
+    A_RES = 0, A_NF, A_DPHI, A_A, A_Q4, A_N2, A_RPR, A_RPPR, A_PRPHI, A_PRPR, A_PRPP, A_RPP, A_PPPHI, A_PPPP,
+    A_RPHI, A_PHIPHI, A_K
 };
+constexpr int kResidSums = A_RPR;
 constexpr unsigned A_MAXMASK = (1u << A_RES) | (1u << A_NF) | (1u << A_DPHI);
 
-// Phase B sums: rotation forms, <phat, L phat>, <phi, L phat>, and the line-search polynomials.
+// Phase B sums: rotation forms (formed by the x and y passes), then <phat, L phat>, <phi, L phat> and the
+// line-search polynomials (by the last pass).  A pass reduces only the entries that it forms and
+// writes zeros for the others.
 enum : int {
     B_CR = 0, B_AR, B_BR, B_C, B_B, B_AA, B_AB, B_ACA, B_CACA, B_CAB, B_BB, B_AC, B_SB, B_SC, B_NF,
     B_K = 15
 };
+constexpr int kRotSums = B_C;
 constexpr unsigned B_MAXMASK = 1u << B_NF;
-
 
 // Pending retraction step of the previous iteration, applied pointwise at the start of phase A:
 // phi <- c_phi phi + c_p p, L phi <- c_L L phi + c_Lp L phat (linearity of L), with the fresh
@@ -147,36 +152,37 @@ __device__ __forceinline__ void res_sums(double* acc, C2<T> r) {
     if (!isfinite(m2)) acc[A_NF] = 1.0;
 }
 
-template <typename T>
+// (OFF: the entry that acc[0] stands for)
+template <typename T, int OFF = 0>
 __device__ __forceinline__ void cg_sums(double* acc, C2<T> r, C2<T> pr, C2<T> rp, C2<T> pp, C2<T> ph) {
-    acc[A_RPR] += (double)redot(r, pr);
-    acc[A_RPPR] += (double)redot(rp, pr);
-    acc[A_PRPHI] += (double)redot(pr, ph);
-    acc[A_PRPR] += (double)abs2(pr);
-    acc[A_PRPP] += (double)redot(pr, pp);
-    acc[A_RPP] += (double)redot(r, pp);
-    acc[A_PPPHI] += (double)redot(pp, ph);
-    acc[A_PPPP] += (double)abs2(pp);
-    acc[A_RPHI] += (double)redot(r, ph);
-    acc[A_PHIPHI] += (double)abs2(ph);
+    acc[A_RPR - OFF] += (double)redot(r, pr);
+    acc[A_RPPR - OFF] += (double)redot(rp, pr);
+    acc[A_PRPHI - OFF] += (double)redot(pr, ph);
+    acc[A_PRPR - OFF] += (double)abs2(pr);
+    acc[A_PRPP - OFF] += (double)redot(pr, pp);
+    acc[A_RPP - OFF] += (double)redot(r, pp);
+    acc[A_PPPHI - OFF] += (double)redot(pp, ph);
+    acc[A_PPPP - OFF] += (double)abs2(pp);
+    acc[A_RPHI - OFF] += (double)redot(r, ph);
+    acc[A_PHIPHI - OFF] += (double)abs2(ph);
 }
 
 // Line-search sums at one point (A = |phi|^2, B = Re conj(phi) phat, C = |phat|^2; o = L phat).
-template <typename T>
+template <typename T, int OFF = 0>
 __device__ __forceinline__ void linesearch_sums(double* acc, C2<T> ph, C2<T> p, C2<T> o) {
     const double A = abs2(ph), Bq = redot(ph, p), Cq = abs2(p);
-    acc[B_C] += (double)redot(p, o);
-    acc[B_B] += (double)redot(ph, o);
-    acc[B_AA] += A * A;
-    acc[B_AB] += A * Bq;
-    acc[B_ACA] += A * (Cq - A);
-    acc[B_CACA] += (Cq - A) * (Cq - A);
-    acc[B_CAB] += (Cq - A) * Bq;
-    acc[B_BB] += Bq * Bq;
-    acc[B_AC] += A * Cq;
-    acc[B_SB] += Bq;
-    acc[B_SC] += Cq;
-    if (!isfinite((double)o.x) || !isfinite((double)o.y)) acc[B_NF] = 1.0;
+    acc[B_C - OFF] += (double)redot(p, o);
+    acc[B_B - OFF] += (double)redot(ph, o);
+    acc[B_AA - OFF] += A * A;
+    acc[B_AB - OFF] += A * Bq;
+    acc[B_ACA - OFF] += A * (Cq - A);
+    acc[B_CACA - OFF] += (Cq - A) * (Cq - A);
+    acc[B_CAB - OFF] += (Cq - A) * Bq;
+    acc[B_BB - OFF] += Bq * Bq;
+    acc[B_AC - OFF] += A * Cq;
+    acc[B_SB - OFF] += Bq;
+    acc[B_SC - OFF] += Cq;
+    if (!isfinite((double)o.x) || !isfinite((double)o.y)) acc[B_NF - OFF] = 1.0;
 }
 
 // One iteration of 2-D and 3-D instances (r and r_{n-1} trade places after it: the caller swaps them).

@@ -185,7 +185,7 @@ hipError_t enqueue_line(const IterCtx<T>& c, int iters, hipStream_t s) {
     const int lg = g.lg[0];
     const K kern = variants[!g.f5[0] && lg >= 6 && lg <= 9 ? lg - 5 : 0];
     launch_timed(ev, kern, dim3((unsigned)Bl), dim3((unsigned)line_threads(g)), line_lds(g, sizeof(C2<T>)), s, c.f, g,
-                 (const C2<T>*)c.tw->get(0, sizeof(T) == 8), c.S + 2 * c.B,
+                 (const C2<T>*)c.tw->get(0, sizeof(T) == 8), c.S + c.B,
                  c.parts + (size_t)R_B * c.region_doubles, (int)B_K, iters, spectral ? 1 : 0, pre, post);
     return hipGetLastError();
 }

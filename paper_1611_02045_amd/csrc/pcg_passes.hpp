@@ -15,10 +15,11 @@
 // Scalar logic (FP64) runs at the start of the pass that consumes a reduction: every workgroup
 // reduces the previous pass's per-block partials in the same fixed order and runs the same
 // logic, so all workgroups agree bit for bit without atomics, fences or a serial tail; one
-// workgroup per instance publishes the state into a versioned slot (S_step after the step, S_res
-// after the convergence test, S_dir after the CG direction), so no pass writes a slot it reads.
-// The convergence test runs at the start of the first middle pass, beta_cg and the descent test
-// at the start of the direction pass, and the step at the start of the next iteration.  lambda, lambda~ and E of the next iterate follow exactly from the line-search sums
+// workgroup per instance publishes the state into a versioned slot (S_step after the step, S_dir
+// after the convergence test and the CG direction), so no pass writes a slot it reads.
+// The convergence test, beta_cg and the descent test run at the start of the direction pass (the
+// preconditioner's passes of a just converged instance run for nothing), and the step at the start of the
+// next iteration.  lambda, lambda~ and E of the next iterate follow exactly from the line-search sums
 // (they are quadratic and quartic forms in (cos t, sin t)), so the residual of iteration n+1 can
 // be formed in the same pass that applies the step.  Every kernel returns at once for instances
 // whose `done` flag is set, so surplus iterations queued after convergence are no-ops.
@@ -521,7 +522,8 @@ struct OpResid {
     // (measured 15% faster on 640^2)
     static constexpr bool FWD = true, INV = false, SCALARS = true, PREFETCH = true, WIDE = sizeof(T) == 8;
     static constexpr bool WIDE_RT = true;
-    static constexpr int K = A_K;
+    static constexpr int K = kResidSums, ROW = A_K, ROW_AT = 0;
+    static constexpr bool ROW_FILL = false;  // OpPLast's
     static constexpr unsigned MAXMASK = A_MAXMASK;
     IterFields<T> f;
     const Scal* Sin;  // S_dir
@@ -578,29 +580,21 @@ struct OpResid {
 
 // ---------------------------------------------------------------------------------------------
 // Phase A, middle passes (y, z): forward and/or inverse transform with the kinetic multiplier
-// 1/(lambda~ + |k|^2/2) (with the 1/N of the inverse transforms) on the pass that does both.
-// The first middle pass (ABS) runs the convergence test on the first pass's sums, in the block
-// that publishes the instance's state (blk 0) only: the multiplier needs lambda~ alone, which the
-// step already put in S_step, so the other blocks start their transforms without waiting for the
-// reduction.  They also transform the lines of an instance that the test finds converged (their
-// output is never read).
+// 1/(lambda~ + |k|^2/2) (with the 1/N of the inverse transforms) on the pass that does both.  They read
+// lambda~ from S_step alone.  With the convergence test in the first of them (in the block that publishes
+// the state) its registers bound every block of the pass: 128 with 164 bytes of scratch in FP32, 168 with
+// 72 in FP64, against 95 and 112 without it.
 // ---------------------------------------------------------------------------------------------
-template <typename T, int AX, bool F, bool I, bool ABS>
+template <typename T, int AX, bool F, bool I>
 struct OpPMid {
     static constexpr bool FWD = F, INV = I, SCALARS = true, PREFETCH = true, WIDE = false;
     static constexpr bool PREFETCH_EARLY = true;  // w only: eight points per thread
     static constexpr int K = 0;
     static constexpr unsigned MAXMASK = 0;
     C2<T>* w;
-    const Scal* Sin;  // ABS: S_step; otherwise S_res
-    Scal* Sout;       // ABS: S_res
-    Partials pa1;
-    using Intake = std::conditional_t<ABS, IntakeA, IntakeState>;
-    __device__ void intake(int b, int blk, Intake& it) const {
-        it.st.issue(Sin, b);
-        if constexpr (ABS)
-            if (blk == 0) it.rows.issue(pa1, b);
-    }
+    const Scal* Sin;  // S_step
+    using Intake = IntakeState;
+    __device__ void intake(int b, int, Intake& it) const { it.st.issue(Sin, b); }
     struct State {
         C2<T> w[8];
     };
@@ -609,19 +603,7 @@ struct OpPMid {
         for (int q = 0; q < 8; ++q) st.w[q] = w[lc.at(q)];
     }
     __device__ void prefetch_tail(const Geo&, const LineCtx&, State&) const {}
-    __device__ void begin(const Geo&, int b, int blk, double* red, Scal* s, Intake& it) const {
-        if constexpr (ABS) {
-            if (blk == 0) {
-                __shared__ double tot[A_K];
-                absorb_finish(Sin, b, blk, s, it, pa1, red, tot, [](Scal& S, const double* t) {
-                    if (!S.done) fin_residual(S, t);
-                });
-                state_publish(Sout, b, blk, s);
-                return;
-            }
-        }
-        state_copy(Sin, b, s, it.st);
-    }
+    __device__ void begin(const Geo&, int b, int, double*, Scal* s, Intake& it) const { state_copy(Sin, b, s, it.st); }
     __device__ void load(const Geo&, const LineCtx&, State& st, C2<T> (&v)[8], double (&)[1]) const {
 #pragma unroll
         for (int q = 0; q < 8; ++q) v[q] = st.w[q];
@@ -660,10 +642,11 @@ struct OpPMid {
 template <typename T>
 struct OpPLast {
     static constexpr bool FWD = false, INV = true, SCALARS = true, PREFETCH = true, WIDE = sizeof(T) == 8;
-    static constexpr int K = A_K;
-    static constexpr unsigned MAXMASK = A_MAXMASK;
+    static constexpr int K = A_K - kResidSums, ROW = A_K, ROW_AT = kResidSums;
+    static constexpr bool ROW_FILL = false;  // OpResid's
+    static constexpr unsigned MAXMASK = 0;
     IterFields<T> f;
-    const Scal* Sin;  // S_res
+    const Scal* Sin;  // S_step
     int post;
     // w for the transform; the tail: what the epilogue and the CG sums read
     struct State {
@@ -704,7 +687,7 @@ struct OpPLast {
             C2<T> pr = v[q];
             if (post) pr = scl(pr, pscale<T>(post, pv_diag(s, (double)st.V[q], (double)abs2(ph))));
             f.pr[i] = pr;
-            cg_sums<T>(acc, st.r[q], pr, st.rp[q], st.pp[q], ph);
+            cg_sums<T, kResidSums>(acc, st.r[q], pr, st.rp[q], st.pp[q], ph);
         }
     }
 };
@@ -714,19 +697,21 @@ struct OpPLast {
 // L phat = sum_a F_a^{-1}[sigma_a F_a phat] + V phat (V phat with the x part).  When omega != 0 the passes along x and y
 // also transform phi (forward only) to accumulate <phi, R phi>, Re<phi, R phat>, <phat, R phat>
 // (Parseval per line), which keeps lambda~ exact without a separate rotation field.  The first
-// pass runs the CG direction logic (and, on the one-pass paths, the convergence test).
+// pass runs the convergence test and the CG direction logic.
 // ---------------------------------------------------------------------------------------------
 template <typename T, int AX, bool FIRST, bool LAST>
 struct OpLp {
     static constexpr bool FWD = true, INV = true, SCALARS = true, PREFETCH = true, WIDE = true;
     static constexpr bool PHI = FIRST || LAST || AX < 2;  // phi is read (x, y: for the rotation sums when omega != 0)
-    static constexpr int K = B_K;
-    static constexpr unsigned MAXMASK = B_MAXMASK;
+    // the rotation sums of the x and y passes, the line-search sums of the last
+    static constexpr int ROW = B_K, ROW_AT = AX < 2 ? 0 : kRotSums;
+    static constexpr bool ROW_FILL = true;
+    static constexpr int K = (LAST ? B_K : kRotSums) - ROW_AT;
+    static constexpr unsigned MAXMASK = LAST ? B_MAXMASK >> ROW_AT : 0u;
     IterFields<T> f;
-    const Scal* Sin;   // FIRST: S_res (or S_step on the one-pass paths); otherwise S_dir
+    const Scal* Sin;   // FIRST: S_step; otherwise S_dir
     Scal* Sout;        // FIRST: S_dir
-    Partials pres;     // FIRST: set (to pdir's region) when the convergence test runs here (one-pass paths)
-    Partials pdir;     // FIRST: sums for the CG direction
+    Partials pdir;     // FIRST: the phase-A sums
     using Intake = std::conditional_t<FIRST, IntakeA, IntakeState>;
     __device__ void intake(int b, int, Intake& it) const {
         it.st.issue(Sin, b);
@@ -761,24 +746,14 @@ struct OpLp {
     }
     __device__ void begin(const Geo&, int b, int blk, double* red, Scal* s, Intake& it) const {
         if constexpr (FIRST) {
-            // on the one-pass paths the convergence test reads the same region as the direction
             __shared__ double tot[A_K];
-            it.st.store(Sin, b, s);
-            it.rows.reduce(pdir, b, red, tot);
-            auto direction = [](Scal& S, const double* t) {
+            absorb_finish(Sin, b, blk, s, it, pdir, red, tot, [](Scal& S, const double* t) {
+                if (!S.done) fin_residual(S, t);
                 if (!S.done) {
                     fin_direction(S, t);
                     if (!S.done) S.b_phase = 1;
                 }
-            };
-            if (pres.parts) {
-                finish<A_K>(s, tot, blk, [direction](Scal& S, const double* t) {
-                    if (!S.done) fin_residual(S, t);
-                    direction(S, t);
-                });
-            } else {
-                finish<A_K>(s, tot, blk, direction);
-            }
+            });
             state_publish(Sout, b, blk, s);
         } else {
             state_copy(Sin, b, s, it.st);
@@ -838,7 +813,7 @@ struct OpLp {
                 f.w[i] = o;
             } else {
                 f.lp[i] = o;
-                linesearch_sums<T>(acc, st.ph[q], st.p[q], o);
+                linesearch_sums<T, ROW_AT>(acc, st.ph[q], st.p[q], o);
             }
         }
     }
@@ -849,8 +824,8 @@ struct OpLp {
 #define GPE_PCG_X_PASSES(X, T) \
     X(T, 0, (OpResid<T>)) X(T, 0, (OpPLast<T>)) X(T, 0, (OpLp<T, 0, true, false>))
 #define GPE_PCG_YZ_PASSES(X, T)                                                                                  \
-    X(T, 1, (OpPMid<T, 1, true, true, true>)) X(T, 1, (OpPMid<T, 1, true, false, true>))                         \
-    X(T, 2, (OpPMid<T, 2, true, true, false>)) X(T, 1, (OpPMid<T, 1, false, true, false>))                       \
+    X(T, 1, (OpPMid<T, 1, true, true>)) X(T, 1, (OpPMid<T, 1, true, false>))                         \
+    X(T, 2, (OpPMid<T, 2, true, true>)) X(T, 1, (OpPMid<T, 1, false, true>))                       \
     X(T, 1, (OpLp<T, 1, false, true>)) X(T, 1, (OpLp<T, 1, false, false>)) X(T, 2, (OpLp<T, 2, false, true>))
 #define GPE_UNPAREN(...) __VA_ARGS__
 #define GPE_LAUNCH_EXTERN(T, AX, OP)                                                                                \

@@ -345,10 +345,10 @@ hipError_t run_phase(PhaseArgs& pa, IterFields<T> f, std::vector<Scal>& host_S, 
         s = own.s;
     }
     // scalars to the device
-    // three versioned state slots (after the step, after the convergence test, after the direction);
+    // two versioned state slots (after the step; after the convergence test and the direction);
     // an iteration starts from S_dir
-    Scal* S_dir = pa.S + 2 * B;
-    for (int k = 0; k < 3; ++k)
+    Scal* S_dir = pa.S + B;
+    for (int k = 0; k < 2; ++k)
         if ((e = hipMemcpyAsync(pa.S + k * B, host_S.data(), sizeof(Scal) * B, hipMemcpyHostToDevice, s)) != hipSuccess)
             return e;
     if ((e = normalize_all<T>(f, B, N, S_dir, *pa.red, s)) != hipSuccess) return e;
@@ -485,8 +485,8 @@ hipError_t profile_phase(PhaseArgs& pa, IterFields<T> f, std::vector<Scal>& host
     const Geo& g = pa.g;
     const int64_t N = g.N;
     hipError_t e;
-    Scal* S_dir = pa.S + 2 * pa.B;
-    for (int k = 0; k < 3; ++k)
+    Scal* S_dir = pa.S + pa.B;
+    for (int k = 0; k < 2; ++k)
         if ((e = hipMemcpyAsync(pa.S + k * pa.B, host_S.data(), sizeof(Scal) * pa.B, hipMemcpyHostToDevice, s)) !=
             hipSuccess)
             return e;
