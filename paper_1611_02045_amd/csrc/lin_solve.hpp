@@ -22,7 +22,7 @@ hipError_t lin_solve(LinCtx<T>& c, LinS& h, int check_every) {
     const int nq = pass_blocks_per_field(g, last, cb, 1, true);
     const int nz = spectral ? pass_blocks_per_field(g, 0, cb, 1, true) : kLinDiagBlocks;
     const Partials pq{c.rows, nq, nq, 0}, pz{c.rows + 2 * region, nz, nz, 0};
-    const Partials qview = nq <= kAbsorbRows ? pq : Partials{c.rows + region, (nq + kCollapseRows - 1) / kCollapseRows, 0, 0};
+    const Partials qview = nq <= absorb_rows(1) ? pq : Partials{c.rows + region, (nq + kCollapseRows - 1) / kCollapseRows, 0, 0};
     hipError_t e;
     // x, r update (or only the first residual's z when the state says init), preconditioner
     auto update = [&]() -> hipError_t {
@@ -58,7 +58,7 @@ hipError_t lin_solve(LinCtx<T>& c, LinS& h, int check_every) {
         OpLinApply<T, 2, false, true> oz{c.f, S_dir, nullptr, none};
         return launch_pass<T, 2>(g, 1, c.tw->get(2, f64), oz, pq, c.s);
     };
-    auto collapse_z = [&] { return absorbable<Z_K, 0u>(pz, c.rows + 3 * region, 1, g, c.s); };
+    auto collapse_z = [&] { return absorbable<Z_K, 0u>(pz, c.rows + 3 * region, 1, 1, g, c.s); };
     h.omega = c.omega;
     h.it = 0;
     h.done = h.status = h.first = 0;
@@ -70,7 +70,7 @@ hipError_t lin_solve(LinCtx<T>& c, LinS& h, int check_every) {
     for (int64_t it = 0; it <= h.max_it; it += check_every) {
         for (int k = 0; k < check_every; ++k) {
             if ((e = direction(zview)) != hipSuccess) return e;
-            (void)absorbable<Q_K, 0u>(pq, c.rows + region, 1, g, c.s);
+            (void)absorbable<Q_K, 0u>(pq, c.rows + region, 1, 1, g, c.s);
             if ((e = update()) != hipSuccess) return e;
             zview = collapse_z();
         }

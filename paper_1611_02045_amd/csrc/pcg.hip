@@ -66,7 +66,8 @@ hipError_t enqueue_iteration(const IterCtx<T>& c, hipStream_t s) {
     // the view a consumer absorbs: the region itself, or its collapse into a row per kCollapseRows
     auto consumable = [&](const Partials& p, int rc, int K) -> Partials {
         double* const to = c.parts + (size_t)rc * c.region_doubles;
-        return K == A_K ? absorbable<A_K, A_MAXMASK>(p, to, Bl, g, s) : absorbable<B_K, B_MAXMASK>(p, to, Bl, g, s);
+        return K == A_K ? absorbable<A_K, A_MAXMASK>(p, to, c.B, Bl, g, s)
+                        : absorbable<B_K, B_MAXMASK>(p, to, c.B, Bl, g, s);
     };
     const Partials none{nullptr, 0, 0, 0};
     // algorithmic bytes of a launch: `reals` real numbers of sizeof(T) per grid point and instance
@@ -85,7 +86,7 @@ hipError_t enqueue_iteration(const IterCtx<T>& c, hipStream_t s) {
     const Partials pb0{partsB, nbx, nbB, 0}, pb1{partsB, nby, nbB, nbx}, pb2{partsB, nbz, nbB, nbx + nby};
     const Partials pbAll{partsB, nbB, nbB, 0};
     const int nbBc = (nbB + kCollapseRows - 1) / kCollapseRows;
-    const Partials sb = nbB <= kAbsorbRows ? pbAll : Partials{c.parts + (size_t)R_BC * c.region_doubles, nbBc, nbBc, 0};
+    const Partials sb = nbB <= absorb_rows(c.B) ? pbAll : Partials{c.parts + (size_t)R_BC * c.region_doubles, nbBc, nbBc, 0};
     // ---- phase A ----
     int pre = 0, post = 0;
     const bool spectral_p = c.precond == GPE_P_KINETIC || c.precond == GPE_P_COMBINED || c.precond == GPE_P_C1 ||

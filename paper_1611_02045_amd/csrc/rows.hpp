@@ -143,12 +143,19 @@ __global__ __launch_bounds__(256) void k_collapse(const double* parts, int nb, i
     for (int k = threadIdx.x; k < K; k += blockDim.x) out[((size_t)b * split + part) * K + k] = tot[k];
 }
 
-// The rows a consumer absorbs: the region itself up to kAbsorbRows rows per instance, else its collapse
-// into `to` (queued here), a row per kCollapseRows.  Bl: the launched instances.
-constexpr int kAbsorbRows = 256;
+// Rows per instance up to which the consumers of a batch of B absorb a region as it is.  Every workgroup
+// of the consumer reads all of its instance's rows, where a collapse costs one launch of about 6 us: a lone
+// instance takes up to 512 rows (32 iterations, with collapse -> without, us: 640^2 FP64 4833 -> 4622, 1024 x
+// 512 FP64 4550 -> 4190, 64^3 unchanged), more instances, whose consumers have several workgroups per CU, 256
+// (eight FP64 at 640^2, 320 rows: 16250 collapsed, 16660 not).
+inline int absorb_rows(int B) { return B == 1 ? 512 : 256; }
+
+// The rows a consumer absorbs: the region itself up to absorb_rows(), else its collapse into `to` (queued
+// here), a row per kCollapseRows.  B: the instances of the batch, Bl of them launched.
 template <int K, unsigned MASK>
-inline Partials absorbable(const Partials& p, double* to, int Bl, const Geo& g, hipStream_t s) {
-    if (p.nb <= kAbsorbRows) return p;
+inline Partials absorbable(const Partials& p, double* to, int B, int Bl, const Geo& g,
+                           hipStream_t s) {
+    if (p.nb <= absorb_rows(B)) return p;
     const int split = (p.nb + kCollapseRows - 1) / kCollapseRows;
     hipLaunchKernelGGL((k_collapse<K, MASK>), dim3((unsigned)(Bl * split)), dim3(256), 0, s, p.parts, p.nb,
                        p.row_stride(), to, split, g.b0, g.imap);
