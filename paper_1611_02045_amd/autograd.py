@@ -70,11 +70,15 @@ class Energy(torch.autograd.Function):
     def backward(ctx, gE):
         phi, V = ctx.saved_tensors
         plan = plan_for(ctx.grid, ctx.b, ctx.o, _dtype(phi))
-        g = gE.to(V.dtype)
-        if not torch.is_grad_enabled():
-            # every gradient times g in the passes of one H apply; nothing returns to the host
-            return (*plan.energy_grad_scaled(phi, V, g), None)
-        gphi, gV, db, do = plan.energy_grad(phi, V)  # create_graph: keep the products with g differentiable
+        g = gE.to(V.dtype).resolve_neg()
+        if not torch.is_grad_enabled() and type(g) is torch.Tensor and torch._C._has_storage(g):
+            # every gradient times g in the passes of one H apply; synchronised, since the next call of this
+            # (shared) plan may come on another stream
+            out = plan.energy_grad_scaled(phi, V, g)
+            torch.cuda.current_stream(phi.device).synchronize()
+            return (*out, None)
+        # create_graph or a batch of g (no storage of its own): plain products with g
+        gphi, gV, db, do = plan.energy_grad(phi, V)
         return (g * gphi, g * gV, g * torch.tensor(db, dtype=V.dtype, device=V.device),
                 g * torch.tensor(do, dtype=V.dtype, device=V.device), None)
 

@@ -62,3 +62,34 @@ def test_energy_autograd_forms():
     assert torch.allclose(dk, one[3], rtol=1e-13)
     with pytest.raises(RuntimeError):  # not finite
         energy((phi * float("nan")).detach(), V, b, o, grid)
+
+
+def test_energy_backward_accepts_any_incoming_gradient():
+    """A batch of incoming gradients (no storage of its own), a lazily negated one and one on another stream
+    give the products of the plain one, exactly (powers of two)."""
+    torch = pytest.importorskip("torch")
+    from paper_1611_02045_amd import autograd as A
+    prob = Problem(2, (64, 32), (5.0, 4.0), 120.0, 0.6)
+    V = torch.from_numpy(harmonic_potential(prob, (1.0, 1.3))).cuda().requires_grad_()
+    phi = torch.from_numpy(random_field(prob, 3, envelope=0.05)).cuda().requires_grad_()
+    grid = A.Grid(prob.dim, prob.n, prob.L)
+    b, o = (torch.tensor(x, dtype=torch.float64, device="cuda:0", requires_grad=True) for x in (prob.beta, prob.omega))
+    E = A.energy(phi, V, b, o, grid)
+    one = torch.ones((), dtype=torch.float64, device="cuda:0")
+    args = (phi, V, b, o)
+    want = torch.autograd.grad(E, args, one, retain_graph=True)
+    rows = torch.autograd.grad(E, args, torch.stack([one, -2.0 * one]), retain_graph=True, is_grads_batched=True)
+    for w, r in zip(want, rows):
+        assert torch.equal(r[0], w) and torch.equal(r[1], -2.0 * w)
+    neg = torch.complex(one, 2.0 * one).conj().imag
+    assert neg.is_neg()
+    for w, r in zip(want, torch.autograd.grad(E, args, neg, retain_graph=True)):
+        assert torch.equal(r, -2.0 * w)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        E2 = A.energy(phi, V, b, o, grid)
+        got = torch.autograd.grad(E2, args, 4.0 * one)
+    torch.cuda.current_stream().wait_stream(side)
+    for w, r in zip(want, got):
+        assert torch.equal(r, 4.0 * w)
