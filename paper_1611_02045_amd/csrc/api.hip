@@ -171,11 +171,6 @@ int gpe_plan_create(const gpe_problem_t* prob, int dtype, gpe_plan_t** out) {
     hipError_t e = build_twiddles(p->g, p->tw);
     if (e == hipSuccess) e = reduce_init(p->red, 1 << 18, 128);
     if (e == hipSuccess) e = hipGetDevice(&p->device);
-    if (e == hipSuccess) {
-        std::lock_guard<std::mutex> lock(capture_mutex());
-        e = hipHostMalloc((void**)&p->host, sizeof(double) * kHostScalars, hipHostMallocMapped);
-        if (e == hipSuccess) e = hipHostGetDevicePointer((void**)&p->host_dev, p->host, 0);
-    }
     if (e != hipSuccess) {
         set_error(std::string("plan creation failed: ") + hipGetErrorString(e));
         p->release();
@@ -201,6 +196,7 @@ int gpe_plan_destroy(gpe_plan_t* plan) {
 static int energy_impl(gpe_plan_t* plan, const void* phi, const void* V, void* E_dev, double* E, double* parts,
                        void* stream) {
     hipStream_t s = (hipStream_t)stream;
+    HIPCHK(plan->ensure_host());
     HIPCHK(op_energy(plan->g, plan->f64(), plan->tw, phi, V, plan->prob.beta, plan->prob.omega, plan->red,
                      (double*)plan->red.scalars.ptr, s, plan->host_dev, E_dev));
     HIPCHK(hipStreamSynchronize(s));
@@ -345,6 +341,7 @@ int gpe_energy_grad(gpe_plan_t* plan, const void* phi, const void* V, void* grad
     const size_t cb = plan->f64() ? 16 : 8;
     const bool scalars = dE_dbeta || dE_domega;
     HIPCHK(plan->tmp.ensure(cb * (size_t)plan->g.N));
+    if (scalars) HIPCHK(plan->ensure_host());
     HIPCHK(op_energy_grad(plan->g, plan->f64(), plan->tw, phi, V, grad_phi, grad_V, plan->prob.beta, plan->prob.omega,
                           plan->red, scalars ? plan->host_dev : nullptr, nullptr, nullptr, nullptr, plan->tmp.ptr, s));
     if (scalars) {

@@ -1,6 +1,9 @@
 // Host-side plan object behind the opaque gpe_plan_t of the C ABI.
 #pragma once
 
+#include <atomic>
+#include <mutex>
+
 #include "internal.hpp"
 
 constexpr int kHostScalars = 16;
@@ -18,8 +21,25 @@ struct gpe_plan {
     gpe::DevBuf scal;              // per-instance solver scalars
     gpe::DevBuf hist;              // per-iteration history rows
     int64_t hist_rows = 0;
-    double* host = nullptr;        // mapped host memory for the scalars a call returns (kHostScalars), and
-    double* host_dev = nullptr;    // its device address: kernels write them there, no copy is queued
+    // mapped host memory for the scalars a call returns (kHostScalars) and its device address: kernels write
+    // them there, no copy is queued.  Made by the first call that returns scalars: the allocation took 60-130 us
+    // of every plan's creation.
+    std::atomic<double*> host{nullptr};
+    double* host_dev = nullptr;
+    hipError_t ensure_host() {
+        if (host.load(std::memory_order_acquire)) return hipSuccess;
+        std::lock_guard<std::mutex> lock(gpe::capture_mutex());
+        if (host.load(std::memory_order_relaxed)) return hipSuccess;
+        double* p = nullptr;
+        hipError_t e = hipHostMalloc((void**)&p, sizeof(double) * kHostScalars, hipHostMallocMapped);
+        if (e != hipSuccess) return e;
+        if ((e = hipHostGetDevicePointer((void**)&host_dev, p, 0)) != hipSuccess) {
+            (void)hipHostFree(p);
+            return e;
+        }
+        host.store(p, std::memory_order_release);
+        return hipSuccess;
+    }
     bool f64() const { return dtype == GPE_F64; }
     void release() {
         tw.release();
@@ -30,10 +50,10 @@ struct gpe_plan {
         solver32.release();
         scal.release();
         hist.release();
-        if (host) {
+        if (double* const p = host.exchange(nullptr)) {
             std::lock_guard<std::mutex> lock(gpe::capture_mutex());
-            (void)hipHostFree(host);
+            (void)hipHostFree(p);
         }
-        host = host_dev = nullptr;
+        host_dev = nullptr;
     }
 };
