@@ -83,6 +83,32 @@ __host__ __device__ __forceinline__ void dft8(C2<T> (&v)[8]) {
     v[1] = b0; v[3] = b1; v[5] = b2; v[7] = b3;
 }
 
+__host__ __device__ __forceinline__ float fma_of(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__host__ __device__ __forceinline__ double fma_of(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// dft8 with the roundings of its outputs 3 and 7 fixed: the pair of twiddled differences b1 e^{..}, b3 e^{..}
+// enters their sum by a fused multiply-add and their difference as rounded products.  In dft8 itself the
+// compiler fuses a product into each addition that lies in the same basic block, so the same transform rounds
+// differently under another epilogue; see line_fft.
+template <typename T, int DIR>
+__host__ __device__ __forceinline__ void dft8_fixed(C2<T> (&v)[8]) {
+#pragma clang fp contract(off)
+    const T c = (T)0.707106781186547524400844362104849039;
+    C2<T> a0 = add(v[0], v[4]), b0 = sub(v[0], v[4]);
+    C2<T> a1 = add(v[1], v[5]), b1 = sub(v[1], v[5]);
+    C2<T> a2 = add(v[2], v[6]), b2 = sub(v[2], v[6]);
+    C2<T> a3 = add(v[3], v[7]), b3 = sub(v[3], v[7]);
+    b1 = DIR < 0 ? mk(b1.x + b1.y, b1.y - b1.x) : mk(b1.x - b1.y, b1.x + b1.y);                  // / c
+    b2 = rot90<T, DIR>(b2);
+    b3 = DIR < 0 ? mk(c * (b3.y - b3.x), -c * (b3.x + b3.y)) : mk(-c * (b3.x + b3.y), c * (b3.x - b3.y));
+    const C2<T> s = mk(fma_of(c, b1.x, b3.x), fma_of(c, b1.y, b3.y));
+    const C2<T> d = rot90<T, DIR>(mk(c * b1.x - b3.x, c * b1.y - b3.y));
+    const C2<T> e = add(b0, b2), f = sub(b0, b2);
+    dft4<T, DIR>(a0, a1, a2, a3);
+    v[0] = a0; v[2] = a1; v[4] = a2; v[6] = a3;
+    v[1] = add(e, s); v[3] = add(f, d); v[5] = sub(e, s); v[7] = sub(f, d);
+}
+
 // In-place 5-point DFT: X_k = sum_r x_r e^{DIR 2 pi i rk/5}.  With c_m = cos(2 pi m/5),
 // s_m = sin(2 pi m/5): X_1,4 = x0 + c1 (x1 + x4) + c2 (x2 + x3) +- DIR i (s1 (x1 - x4) + s2 (x2 - x3))
 // and X_2,3 = x0 + c2 (x1 + x4) + c1 (x2 + x3) +- DIR i (s2 (x1 - x4) - s1 (x2 - x3)).
@@ -233,8 +259,8 @@ __device__ __forceinline__ void fft_line(C2<T> (&v)[8], C2<T>* buf, const C2<T>*
 // and stage count a constant (LDS addresses become immediate offsets).  WAVE: lines lie within one
 // wave.  CS > 0: point i of the line's LDS region sits at buf[i * CS] instead of the padded
 // buf[lpad(i)] (a column of a plane held in LDS, whose neighbouring columns go to neighbouring
-// lanes, so the stride needs no padding).
-template <typename T, int DIR, int LG, bool WAVE, bool F5 = false, int CS = 0>
+// lanes, so the stride needs no padding).  FIXED: the last stage is dft8_fixed (lines of 2^LG points).
+template <typename T, int DIR, int LG, bool WAVE, bool F5 = false, int CS = 0, bool FIXED = false>
 __device__ __forceinline__ void fft_line_ct(C2<T> (&v)[8], C2<T>* buf, const C2<T>* tw, int t) {
     static_assert(LG >= 3 && LG <= 10, "lines of 8 to 1024 points");
     static_assert(!F5 || (LG <= 7 && !WAVE), "lines of 5 * 2^LG points: at most 640, across waves");
@@ -296,7 +322,11 @@ __device__ __forceinline__ void fft_line_ct(C2<T> (&v)[8], C2<T>* buf, const C2<
             v[6] = mul(v[6], mul(w2, w4));
             v[7] = mul(v[7], mul(w3, w4));
         }
-        dft8<T, DIR>(v);
+        if constexpr (FIXED && !F5) {
+            if (k + 1 == N8) dft8_fixed<T, DIR>(v); else dft8<T, DIR>(v);
+        } else {
+            dft8<T, DIR>(v);
+        }
         if (k + 1 < N8 || F5) {
             const int base = ((t >> lgNs) << (lgNs + 3)) + (t & (Ns - 1));
 #pragma unroll

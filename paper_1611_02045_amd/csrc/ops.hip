@@ -23,7 +23,7 @@ namespace gpe {
 // 256^2 FP64 field).
 template <typename T, int AX>
 struct OpApply {
-    static constexpr bool FWD = true, INV = true, SCALARS = false, PREFETCH = true, WIDE = false;
+    static constexpr bool FWD = true, INV = true, SCALARS = false, PREFETCH = true, WIDE = false, FIXED = true;
     static constexpr int K = 0;
     static constexpr unsigned MAXMASK = 0;
     const C2<T>* f;
@@ -463,7 +463,7 @@ static hipError_t energy_t(const Geo& g, const Twiddles& tw, const void* phi, co
 // ---------------------------------------------------------------------------------------------
 template <typename T, int AX, bool LAST>
 struct OpEnergyGrad {
-    static constexpr bool FWD = true, INV = true, SCALARS = false, PREFETCH = true, WIDE = false;
+    static constexpr bool FWD = true, INV = true, SCALARS = false, PREFETCH = true, WIDE = false, FIXED = true;
     static constexpr int K = AX < 2 ? 2 : 0;  // {quartic, rotation}
     static constexpr int KA = K > 0 ? K : 1;
     static constexpr unsigned MAXMASK = 0;
@@ -616,7 +616,7 @@ hipError_t op_lambda_tilde(const double* parts, double* dst, hipStream_t s) {
 // ---------------------------------------------------------------------------------------------
 template <typename T, int AX, bool F, bool I>
 struct OpPre {
-    static constexpr bool FWD = F, INV = I, SCALARS = false, PREFETCH = true, WIDE = false;
+    static constexpr bool FWD = F, INV = I, SCALARS = false, PREFETCH = true, WIDE = false, FIXED = true;
     static constexpr int K = 0;
     static constexpr unsigned MAXMASK = 0;
     // only the x passes scale: the prologue's and the epilogue's V and phi (1-D does both)

@@ -133,11 +133,14 @@ __device__ __forceinline__ LineCtx decode_line(const Geo& g, int C, int& blk) {
     return lc;
 }
 
-// The line transform of a pass: the compile-time form for LG > 0, else the run-time one.
-template <typename T, int DIR, int AX, int LG>
+// The line transform of a pass: the compile-time form for LG > 0, else the run-time one.  FIXED: the last
+// stage rounds the same in every pass (dft8_fixed).  The operators' passes ask for it in the transform that
+// ends them: there dft8 would round by how the compiler lays out the epilogue, and L phi is where an FP32
+// solve starts and is refreshed from, so that a new epilogue moved whole FP32 trajectories.
+template <typename T, int DIR, int AX, int LG, bool FIXED = false>
 __device__ __forceinline__ void line_fft(C2<T> (&v)[8], C2<T>* buf, const C2<T>* tw, const LineCtx& lc) {
     if constexpr (LG > 0)
-        fft_line_ct<T, DIR, ct_lg(LG), AX == 0 && !ct_f5(LG) && ct_lg(LG) <= 9, ct_f5(LG)>(v, buf, tw, lc.t);
+        fft_line_ct<T, DIR, ct_lg(LG), AX == 0 && !ct_f5(LG) && ct_lg(LG) <= 9, ct_f5(LG), 0, FIXED>(v, buf, tw, lc.t);
     else
         fft_line<T, DIR>(v, buf, tw, lc.t, lc.lg, lc.M, lc.wave);
 }
@@ -224,6 +227,16 @@ struct PrefetchEarly {
 template <class Op>
 struct PrefetchEarly<Op, std::void_t<decltype(Op::PREFETCH_EARLY)>> {
     static constexpr bool value = Op::PREFETCH_EARLY;
+};
+
+// Whether the last transform of an Op has its roundings fixed (Op::FIXED when the Op defines it; see line_fft).
+template <class Op, class = void>
+struct FixedRounding {
+    static constexpr bool value = false;
+};
+template <class Op>
+struct FixedRounding<Op, std::void_t<decltype(Op::FIXED)>> {
+    static constexpr bool value = Op::FIXED;
 };
 
 // Entries per partial row and the first that the Op writes (Op::ROW, Op::ROW_AT; default: its K sums are
@@ -343,9 +356,10 @@ void pass_kernel(Geo g, int C, const C2<T>* __restrict__ twg, Op op, Partials pr
 
     const C2<T>* twx = kTwGlobal ? twg : tw;
     op.load(g, lc, st, v, acc);
-    if (Op::FWD) line_fft<T, -1, AX, LG>(v, buf, twx, lc);
+    constexpr bool kFixed = FixedRounding<Op>::value;
+    if (Op::FWD) line_fft<T, -1, AX, LG, kFixed && !Op::INV>(v, buf, twx, lc);
     op.template spectral<LG>(g, lc, st, v, acc, buf, twx);
-    if (Op::INV) line_fft<T, +1, AX, LG>(v, buf, twx, lc);
+    if (Op::INV) line_fft<T, +1, AX, LG, kFixed>(v, buf, twx, lc);
     if constexpr (!EARLY && Op::PREFETCH) op.prefetch_tail(g, lc, st);
     op.store(g, lc, st, v, acc);
 
