@@ -8,6 +8,7 @@
 #include <vector>
 
 #include "internal.hpp"
+#include "launch.hpp"
 #include "plan.hpp"
 
 namespace gpe {
@@ -169,7 +170,7 @@ int gpe_plan_create(const gpe_problem_t* prob, int dtype, gpe_plan_t** out) {
     p->dtype = dtype;
     p->g = make_geo(*prob);
     hipError_t e = build_twiddles(p->g, p->tw);
-    if (e == hipSuccess) e = reduce_init(p->red, 1 << 18, 128);
+    if (e == hipSuccess) e = reduce_init(p->red, field_part_doubles(p->g, p->f64() ? 16 : 8), 128);
     if (e == hipSuccess) e = hipGetDevice(&p->device);
     if (e != hipSuccess) {
         set_error(std::string("plan creation failed: ") + hipGetErrorString(e));

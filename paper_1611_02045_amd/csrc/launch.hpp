@@ -133,6 +133,28 @@ inline int pass_blocks_per_field(const Geo& g, int AX, int complex_bytes, int B,
     return (int)(lines_per_field(g, AX) / pass_lines_per_block(g, AX, complex_bytes, B, solver));
 }
 
+// Fewest lines per workgroup that a tile measurement tries: whole waves where the grid allows it (a partial
+// wave idles lanes).
+inline int fewest_tuned_lines(const Geo& g, int AX, int complex_bytes) {
+    int C = 1;
+    while (C * (g.n[AX] / 8) < 64 && valid_lines(g, AX, complex_bytes, 2 * C)) C *= 2;
+    return C;
+}
+
+// Most workgroups of an operator pass over one field, whatever tile was measured.
+inline int64_t most_blocks(const Geo& g, int AX, int complex_bytes) {
+    return lines_per_field(g, AX) /
+           std::min(pass_lines_rule(g, AX, complex_bytes, 1), fewest_tuned_lines(g, AX, complex_bytes));
+}
+
+// Doubles that the partial rows of an operator on one field can take: the energy's four sums in every pass.  At
+// least 1 << 18, which covers 1-D and 2-D grids and 3-D ones of up to some 10^7 points.
+inline size_t field_part_doubles(const Geo& g, int complex_bytes) {
+    size_t rows = 0;
+    for (int a = 0; a < g.dim; ++a) rows += (size_t)most_blocks(g, a, complex_bytes);
+    return std::max<size_t>(1 << 18, 4 * rows);
+}
+
 // Launch one pass over B instances.  `pr` receives nb (blocks per instance) if the Op reduces.
 template <typename T, int AX, class Op>
 hipError_t launch_pass(const Geo& g, int B, const void* tw, const Op& op, Partials pr, hipStream_t s,

@@ -300,10 +300,7 @@ static hipError_t tune_axis(const Geo& g, int B, const Twiddles& tw, const C2<T>
     if ((e = hipEventCreate(&e1)) != hipSuccess) return e;
     best_C = 0;
     best_us = 0.0;
-    // whole waves where the grid allows it (a partial wave idles lanes)
-    int Cmin = 1;
-    while (Cmin * TPL < 64 && valid_lines(g, AX, cb, 2 * Cmin)) Cmin *= 2;
-    for (int C = Cmin; C * TPL <= max_pass_threads(g, AX) && e == hipSuccess; C *= 2) {
+    for (int C = fewest_tuned_lines(g, AX, cb); C * TPL <= max_pass_threads(g, AX) && e == hipSuccess; C *= 2) {
         if (!valid_lines(g, AX, cb, C)) continue;
         constexpr int kWarm = 2, kReps = 10;
         for (int r = 0; r < kWarm && e == hipSuccess; ++r) e = launch_pass<T, AX>(g, B, tw.get(AX, sizeof(T) == 8), op, none, s, nullptr, C);
@@ -426,6 +423,19 @@ __global__ __launch_bounds__(256) void k_energy_collect(const double* p0, int n0
     }
 }
 
+// Row regions of the passes along axes [0, axes) of one field, K sums per row: the tiles C and row counts nb,
+// settled once for the launches and their consumer (another thread may record a tile meanwhile).  Fails when the
+// rows exceed the buffer.
+static hipError_t field_rows(const Geo& g, int complex_bytes, int axes, int K, const Reduce& red, int C[3], int nb[3]) {
+    size_t rows = 0;
+    for (int a = 0; a < axes; ++a) {
+        C[a] = pass_lines_per_block(g, a, complex_bytes, 1, false);
+        nb[a] = (int)(lines_per_field(g, a) / C[a]);
+        rows += (size_t)nb[a];
+    }
+    return sizeof(double) * rows * K <= red.parts.bytes ? hipSuccess : hipErrorInvalidValue;
+}
+
 template <typename T>
 static hipError_t energy_t(const Geo& g, const Twiddles& tw, const void* phi, const void* V, double beta,
                            double omega, Reduce& red, double* dst, double* host, void* E, hipStream_t s) {
@@ -433,20 +443,19 @@ static hipError_t energy_t(const Geo& g, const Twiddles& tw, const void* phi, co
     const int cb = (int)sizeof(C2<T>);
     const C2<T>* P = (const C2<T>*)phi;
     double* parts = (double*)red.parts.ptr;
-    size_t off = 0;
     const double* pp[3] = {nullptr, nullptr, nullptr};
-    int nn[3] = {0, 0, 0};
+    int nn[3] = {0, 0, 0}, C[3];
     hipError_t e;
+    if ((e = field_rows(g, cb, g.dim, 4, red, C, nn)) != hipSuccess) return e;
+    size_t off = 0;
     for (int ax = 0; ax < g.dim; ++ax) {
         Partials pr{parts + off, 0, 0, 0};
-        const int nb = pass_blocks_per_field(g, ax, cb, 1, false);
-        if (ax == 0) e = launch_pass<T, 0>(g, 1, tw.get(0, f64), OpEnergy<T, 0>{P, (const T*)V, omega}, pr, s);
-        else if (ax == 1) e = launch_pass<T, 1>(g, 1, tw.get(1, f64), OpEnergy<T, 1>{P, (const T*)V, omega}, pr, s);
-        else e = launch_pass<T, 2>(g, 1, tw.get(2, f64), OpEnergy<T, 2>{P, (const T*)V, omega}, pr, s);
+        if (ax == 0) e = launch_pass<T, 0>(g, 1, tw.get(0, f64), OpEnergy<T, 0>{P, (const T*)V, omega}, pr, s, nullptr, C[0]);
+        else if (ax == 1) e = launch_pass<T, 1>(g, 1, tw.get(1, f64), OpEnergy<T, 1>{P, (const T*)V, omega}, pr, s, nullptr, C[1]);
+        else e = launch_pass<T, 2>(g, 1, tw.get(2, f64), OpEnergy<T, 2>{P, (const T*)V, omega}, pr, s, nullptr, C[2]);
         if (e != hipSuccess) return e;
         pp[ax] = parts + off;
-        nn[ax] = nb;
-        off += (size_t)nb * 4;
+        off += (size_t)nn[ax] * 4;
     }
     hipLaunchKernelGGL(k_energy_collect<T>, dim3(1), dim3(256), 0, s, pp[0], nn[0], pp[1], nn[1], pp[2], nn[2],
                        g.cell, beta, dst, host, (T*)E);
@@ -561,23 +570,25 @@ static hipError_t energy_grad_t(const Geo& g, const Twiddles& tw, const void* ph
     const C2<T>* F = (const C2<T>*)phi;
     C2<T>*const O = (C2<T>*)gphi, *const W = (C2<T>*)tmp;
     const T *const Vt = (const T*)V, *const ge = (const T*)gE;
-    const int n0 = pass_blocks_per_field(g, 0, cb, 1, false), n1 = g.dim > 1 ? pass_blocks_per_field(g, 1, cb, 1, false) : 0;
+    int nn[3] = {0, 0, 0}, C[3];
+    hipError_t e = field_rows(g, cb, std::min(g.dim, 2), 2, red, C, nn);
+    if (e != hipSuccess) return e;
+    const int n0 = nn[0], n1 = nn[1];
     double* const p0 = (double*)red.parts.ptr;
     double* const p1 = p0 + 2 * (size_t)n0;
     const Partials r0{p0, n0, n0, 0}, r1{p1, n1, n1, 0}, none{nullptr, 0, 0, 0};
-    hipError_t e;
     if (g.dim == 1) {
         OpEnergyGrad<T, 0, true> ox{F, nullptr, O, Vt, (T*)gV, ge, beta, omega};
-        e = launch_pass<T, 0>(g, 1, tw.get(0, f64), ox, r0, s);
+        e = launch_pass<T, 0>(g, 1, tw.get(0, f64), ox, r0, s, nullptr, C[0]);
     } else {
         OpEnergyGrad<T, 0, false> ox{F, nullptr, W, Vt, (T*)gV, ge, beta, omega};
-        e = launch_pass<T, 0>(g, 1, tw.get(0, f64), ox, r0, s);
+        e = launch_pass<T, 0>(g, 1, tw.get(0, f64), ox, r0, s, nullptr, C[0]);
         if (e == hipSuccess && g.dim == 2) {
             OpEnergyGrad<T, 1, true> oy{F, W, O, nullptr, nullptr, ge, beta, omega};
-            e = launch_pass<T, 1>(g, 1, tw.get(1, f64), oy, r1, s);
+            e = launch_pass<T, 1>(g, 1, tw.get(1, f64), oy, r1, s, nullptr, C[1]);
         } else if (e == hipSuccess) {
             OpEnergyGrad<T, 1, false> oy{F, W, W, nullptr, nullptr, ge, beta, omega};
-            e = launch_pass<T, 1>(g, 1, tw.get(1, f64), oy, r1, s);
+            e = launch_pass<T, 1>(g, 1, tw.get(1, f64), oy, r1, s, nullptr, C[1]);
             OpEnergyGrad<T, 2, true> oz{F, W, O, nullptr, nullptr, ge, beta, omega};
             if (e == hipSuccess) e = launch_pass<T, 2>(g, 1, tw.get(2, f64), oz, none, s);
         }
