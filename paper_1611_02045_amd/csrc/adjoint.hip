@@ -136,7 +136,7 @@ static int adjoint_impl(gpe_plan_t* plan, const void* phi_star, const void* V, c
         report->status = st;
         report->iters = hs.it;
         report->lambda = hs.lam;
-        report->res_inf = hs.rr0 > 0.0 ? std::sqrt(hs.rr / hs.rr0) : 0.0;
+        report->res_inf = hs.rr0 == 0.0 ? 0.0 : std::sqrt(hs.rr / hs.rr0);
         report->seconds = std::chrono::duration<double>(t1 - t0).count();
     }
     if (st == GPE_EINVAL) set_error("the projected Hessian is not positive definite (phi_star is not a local minimum)");

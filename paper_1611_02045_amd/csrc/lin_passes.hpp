@@ -75,6 +75,10 @@ __device__ __forceinline__ void lin_dir(LinS& S, const double* t) {
         S.first = 0;
         S.b = 0.0;
         if (S.hess) S.rr0 = rr;  // relative to the projected right-hand side
+        if (!isfinite(rr) || !isfinite(rz)) {
+            S.status = -4;
+            S.done = 1;
+        }
         // zero right-hand side, or an initial guess that already solves the system
         if (S.hess ? !(S.rr0 > 0.0) : rr <= S.tol2 * S.rr0) S.done = 1;
         S.rz = rz;
@@ -110,7 +114,7 @@ __device__ __forceinline__ void lin_upd(LinS& S, const double* t) {
     S.c1 = S.hess ? w * t[Q_IPHIQ] / S.nphi2 : 0.0;
     const double pq = w * (t[Q_PQ] - S.c0 * t[Q_PPHI] - S.c1 * t[Q_PIPHI]);
     if (!(pq > 0.0)) {
-        S.status = -1;  // the operator is not positive definite
+        S.status = pq != pq ? -4 : -1;  // -1: the operator is not positive definite
         S.done = 1;
         return;
     }
