@@ -39,10 +39,11 @@ struct BatchWork {
     Geo g;                 // shared grid (n); box, beta and omega are per instance in the scalars
     const Twiddles* tw;
     Reduce* red;
-    DevBuf* scal;          // B solver scalars
+    DevBuf* scal;          // solver scalars: two slots of B
     DevBuf* f64;           // FP64 fields (B instances)
     DevBuf* f32;           // FP32 fields (B instances)
     DevBuf* tmp;           // verification scratch (2 fields of one instance)
+    HostBuf* poll;         // polled states
     bool own_stream = false;  // the stream is a non-blocking one of this library's (graphs are captured on it)
 };
 
@@ -54,6 +55,7 @@ int run(BatchWork& w, int B, IterFields<T> f, std::vector<Scal>& hs, const gpe_p
     pa.tw = w.tw;
     pa.S = (Scal*)w.scal->ptr;
     pa.red = w.red;
+    pa.poll = w.poll;
     pa.region_doubles = region_doubles_for(w.g, B);
     pa.precond = o.precond;
     pa.check_every = o.check_every;
@@ -99,6 +101,7 @@ int profile_group(ProfileWork& w, int B, const gpe_problem_t* probs, bool in_f64
     pa.red = w.red;
     pa.region_doubles = region_doubles_for(g, B);
     pa.precond = o.precond;
+    pa.poll = nullptr;
     pa.check_every = 1;
     pa.refresh_every = 0;
     pa.final_f_r_is_rp = false;
@@ -313,10 +316,11 @@ int solve_group(int B, const gpe_problem_t* gp, bool in_f64, const void* const* 
     Twiddles tw;
     Reduce red;
     DevBuf scal, f64, f32, tmp;
+    HostBuf poll;
     int st;
     hipError_t e = build_twiddles(g, tw);
     if (e == hipSuccess) {
-        BatchWork w{g, &tw, &red, &scal, &f64, &f32, &tmp, own_stream};
+        BatchWork w{g, &tw, &red, &scal, &f64, &f32, &tmp, &poll, own_stream};
         st = solve_batch(w, B, gp, in_f64, gV, gphi, o, nullptr, 0, rep, s);
     } else {
         set_error(std::string("twiddle tables: ") + hipGetErrorString(e));
@@ -330,6 +334,7 @@ int solve_group(int B, const gpe_problem_t* gp, bool in_f64, const void* const* 
     f64.release();
     f32.release();
     tmp.release();
+    poll.release();
     return st;
 }
 
@@ -471,7 +476,7 @@ int gpe_pcg_solve(gpe_plan_t* plan, const void* V, void* phi_inout, const gpe_pc
         hist = (double*)plan->hist.ptr;
     }
     BatchWork w{plan->g, &plan->tw, &plan->red, &plan->scal, &plan->solver, plan->f64() ? &plan->solver32 : &plan->solver,
-                &plan->tmp};
+                &plan->tmp, &plan->poll};
     const void* Vs[1] = {V};
     void* phis[1] = {phi_inout};
     st = solve_batch(w, 1, &plan->prob, plan->f64(), Vs, phis, o, hist, cap, report, s);

@@ -42,6 +42,32 @@ struct DevBuf {
     }
 };
 
+// Mapped host memory: kernels write it through `dev`, the host reads `ptr`.  Grows on demand, like DevBuf.
+struct HostBuf {
+    void *ptr = nullptr, *dev = nullptr;
+    size_t bytes = 0;
+    hipError_t ensure(size_t need) {
+        if (need <= bytes) return hipSuccess;
+        release();
+        std::lock_guard<std::mutex> lock(capture_mutex());
+        hipError_t e = hipHostMalloc(&ptr, need, hipHostMallocMapped);
+        if (e != hipSuccess) {
+            ptr = nullptr;
+            return e;
+        }
+        bytes = need;
+        return hipHostGetDevicePointer(&dev, ptr, 0);
+    }
+    void release() {
+        if (ptr) {
+            std::lock_guard<std::mutex> lock(capture_mutex());
+            (void)hipHostFree(ptr);
+        }
+        ptr = dev = nullptr;
+        bytes = 0;
+    }
+};
+
 // Twiddle tables exp(-2 pi i e / M), e < M, for each axis, in both precisions, in one buffer (one upload);
 // axes of equal length share theirs.
 struct Twiddles {

@@ -20,6 +20,7 @@ struct gpe_plan {
     gpe::DevBuf solver32;          // FP32 solver fields of a mixed-precision solve
     gpe::DevBuf scal;              // per-instance solver scalars
     gpe::DevBuf hist;              // per-iteration history rows
+    gpe::HostBuf poll;             // solver states as the host polls them
     int64_t hist_rows = 0;
     // mapped host memory for the scalars a call returns (kHostScalars) and its device address: kernels write
     // them there, no copy is queued.  Made by the first call that returns scalars: the allocation took 60-130 us
@@ -50,6 +51,7 @@ struct gpe_plan {
         solver32.release();
         scal.release();
         hist.release();
+        poll.release();
         if (double* const p = host.exchange(nullptr)) {
             std::lock_guard<std::mutex> lock(gpe::capture_mutex());
             (void)hipHostFree(p);

@@ -284,32 +284,51 @@ __global__ __launch_bounds__(64) void k_poll(const Scal* S, Scal* host) {
     for (int c = threadIdx.x; c < (int)(sizeof(Scal) / sizeof(uint4)); c += 64) dst[c] = src[c];
 }
 
-// Two slots of mapped host memory for the states at the end of a chunk, each with the event that tells
-// when its copy is complete.
+// Slots of mapped host memory for the states, each with the event that tells when its copy is complete: two for
+// the ends of chunks, kMarks for the quarters of the first one.  The memory is the caller's: its allocation and
+// release in each solve took 40 us.
 struct PollSlots {
+    static constexpr int kMarks = 3, kSlots = 2 + kMarks;
     int B = 0;
     Scal *host = nullptr, *dev = nullptr;
-    hipEvent_t ev[2] = {nullptr, nullptr};
+    hipEvent_t ev[kSlots] = {};
     hipStream_t stream = nullptr;
-    bool used = false;
-    hipError_t init(int count, hipStream_t s) {
+    bool used[kSlots] = {};
+    hipError_t init(HostBuf& buf, int count, hipStream_t s) {
         B = count;
         stream = s;
+        hipError_t e = buf.ensure(kSlots * sizeof(Scal) * (size_t)B);
+        if (e != hipSuccess) return e;
+        host = (Scal*)buf.ptr;
+        dev = (Scal*)buf.dev;
         std::lock_guard<std::mutex> lock(capture_mutex());
-        hipError_t e = hipHostMalloc((void**)&host, 2 * sizeof(Scal) * (size_t)B, hipHostMallocMapped);
-        if (e != hipSuccess) {
-            host = nullptr;
-            return e;
-        }
-        e = hipHostGetDevicePointer((void**)&dev, host, 0);
-        for (int k = 0; k < 2 && e == hipSuccess; ++k) e = hipEventCreateWithFlags(&ev[k], hipEventDisableTiming);
+        for (int k = 0; k < kSlots && e == hipSuccess; ++k) e = hipEventCreateWithFlags(&ev[k], hipEventDisableTiming);
         return e;
     }
     hipError_t queue(const Scal* S, int slot) {
-        used = true;
+        used[slot] = true;
         hipLaunchKernelGGL(k_poll, dim3((unsigned)B), dim3(64), 0, stream, S, dev + (size_t)slot * B);
         const hipError_t e = hipGetLastError();
         return e != hipSuccess ? e : hipEventRecord(ev[slot], stream);
+    }
+    // whether the slot's copy is complete (an error of the device is left to wait())
+    bool ready(int slot) const {
+        if (!used[slot]) return false;
+        const bool yes = hipEventQuery(ev[slot]) != hipErrorNotReady;
+        if (!yes) (void)hipGetLastError();  // "not ready" is no error of a later launch
+        return yes;
+    }
+    bool all_done(int slot) const {
+        return std::all_of(host + (size_t)slot * B, host + (size_t)(slot + 1) * B, [](const Scal& s) { return s.done != 0; });
+    }
+    // whether every instance of slot b is done, or will be after as many iterations again as from slot a to b, its
+    // residual falling as it did there (within a factor of ten)
+    bool ending(int a, int b) const {
+        for (int k = 0; k < B; ++k) {
+            const Scal &p = host[(size_t)a * B + k], &q = host[(size_t)b * B + k];
+            if (!q.done && !(q.res * q.res <= 10.0 * q.tol_res * p.res)) return false;
+        }
+        return true;
     }
     hipError_t wait(int slot, std::vector<Scal>& out) {
         const hipError_t e = hipEventSynchronize(ev[slot]);
@@ -318,11 +337,10 @@ struct PollSlots {
     }
     // queued kernels may still write the slots (and use what its owner frees after it)
     ~PollSlots() {
-        if (used) (void)hipStreamSynchronize(stream);
+        if (std::any_of(used, used + kSlots, [](bool u) { return u; })) (void)hipStreamSynchronize(stream);
         std::lock_guard<std::mutex> lock(capture_mutex());
         for (hipEvent_t x : ev)
             if (x) (void)hipEventDestroy(x);
-        if (host) (void)hipHostFree(host);
     }
 };
 
@@ -395,12 +413,12 @@ hipError_t run_phase(PhaseArgs& pa, IterFields<T> f, std::vector<Scal>& host_S, 
     // work on 256^2).  The chunk after the one that finishes every instance is queued in vain: its
     // kernels return at once.  A chunk's states reach one of two slots of mapped host memory.
     PollSlots poll;
-    if ((e = poll.init(B, s)) != hipSuccess) return e;
+    if ((e = poll.init(*pa.poll, B, s)) != hipSuccess) return e;
     int64_t head = 0, tail = 0;  // chunks queued, chunks polled
     auto queue_chunk = [&]() -> hipError_t {
         // host-side guard: every queued iteration either advances n or finishes the instance
         if (queued > 2 * max_iter + 4 * (int64_t)pa.check_every + 64) return hipErrorUnknown;
-        hipError_t ee;
+        hipError_t ee = hipSuccess;
         if (pa.refresh_every > 0 && since_refresh >= pa.refresh_every) {
             since_refresh = 0;
             for (int b = 0; b < B; ++b) {
@@ -417,19 +435,47 @@ hipError_t run_phase(PhaseArgs& pa, IterFields<T> f, std::vector<Scal>& host_S, 
                     return ee;
             }
         }
-        ee = graph.exec ? graph.launch(s) : enqueue_iterations<T>(c, pa.check_every, s);
+        int left = pa.check_every;
+        const int quarter = pa.check_every / 4;
+        // (1-D: a chunk is one launch; no marks either where a second chunk cannot follow)
+        if (head == 0 && g.dim > 1 && quarter > 0 && pa.check_every <= max_iter)
+            for (int m = 0; m < PollSlots::kMarks; ++m) {
+                if ((ee = enqueue_iterations<T>(c, quarter, s)) != hipSuccess) return ee;
+                if ((ee = poll.queue(S_dir, 2 + m)) != hipSuccess) return ee;
+                left -= quarter;
+            }
+        ee = graph.exec ? graph.launch(s) : enqueue_iterations<T>(c, left, s);
         if (ee != hipSuccess) return ee;
         queued += pa.check_every;
         since_refresh += pa.check_every;
         if ((ee = poll.queue(S_dir, (int)(head & 1))) != hipSuccess) return ee;
         ++head;
-        if (!graph.exec && want_graph && queued <= max_iter)
-            ee = graph.capture(s, [&] { return enqueue_iterations<T>(c, pa.check_every, s); });
         return ee;
+    };
+    // A solve from a (nearly) converged start ends in its first chunk.  If that is seen, from the newest state that
+    // has arrived, by the time the chunk is queued, no graph is captured; and the second chunk is queued at the
+    // first one's last mark, unless it has ended there or is about to.  From the converged field (us; before the
+    // chunks overlapped, with both unconditionally behind the first chunk, now): 256^2 FP64 684, 881, 648; 512^2 831,
+    // 1250, 755; 64^3 1114, 1790, 883.
+    auto first_ended = [&] {
+        for (int slot : {0, 4, 3, 2})
+            if (poll.ready(slot)) return poll.all_done(slot);
+        return false;
     };
     for (;;) {
         if (head == tail && (e = queue_chunk()) != hipSuccess) return e;
-        if (head - tail < 2 && queued <= max_iter && (e = queue_chunk()) != hipSuccess) return e;
+        const bool first = head == 1 && tail == 0 && poll.used[4];
+        if (queued <= max_iter && !(first && first_ended())) {
+            if (!graph.exec && want_graph &&
+                (e = graph.capture(s, [&] { return enqueue_iterations<T>(c, pa.check_every, s); })) != hipSuccess)
+                return e;
+            bool ending = false;
+            if (first) {
+                if ((e = hipEventSynchronize(poll.ev[4])) != hipSuccess) return e;
+                ending = poll.ending(3, 4);
+            }
+            if (head - tail < 2 && !ending && (e = queue_chunk()) != hipSuccess) return e;
+        }
         if ((e = poll.wait((int)(tail & 1), host_S)) != hipSuccess) return e;
         ++tail;
         std::vector<int> run;

@@ -11,8 +11,9 @@ struct PhaseArgs {
     Geo g;
     int B;
     const Twiddles* tw;
-    Scal* S;               // device, B entries
+    Scal* S;               // device, two slots of B entries
     Reduce* red;
+    HostBuf* poll;           // slots of the polled states; they belong to the caller
     size_t region_doubles;
     int precond;
     int check_every;
