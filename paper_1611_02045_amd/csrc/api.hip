@@ -233,7 +233,10 @@ int gpe_apply_H_batched(gpe_plan_t* plan, int count, const void* phi, const void
     if (count < 1) { set_error("count must be >= 1"); return GPE_EINVAL; }
     if (phi == Hphi) { set_error("Hphi must not alias phi"); return GPE_EINVAL; }
     const size_t cb = plan->f64() ? 16 : 8;
-    HIPCHK(plan->tmp.ensure(cb * (size_t)plan->g.N * count));
+    // (not the part's own size, which is not monotone in count: a workspace made by the largest batch of a program
+    // holds its smaller ones, which it may capture)
+    const int64_t fields = std::min<int64_t>(count, apply_part_most(plan->g, (int)cb));
+    HIPCHK(plan->tmp.ensure(cb * (size_t)plan->g.N * (size_t)fields));
     HIPCHK(op_apply(plan->g, plan->f64(), count, plan->tw, phi, V, Hphi, plan->tmp.ptr, plan->prob.beta,
                     plan->prob.omega, true, (hipStream_t)stream));
     return GPE_OK;

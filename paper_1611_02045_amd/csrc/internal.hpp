@@ -91,8 +91,10 @@ hipError_t reduce_init(Reduce& r, size_t part_doubles, size_t scalar_doubles = 6
 // ---------------------------------------------------------------------------------------------
 // Operator launchers (ops.hip).  `f64` selects the precision of the fields (complex128/float64
 // vs complex64/float32).  Fields of B instances are stored back to back.  `tmp` is a workspace
-// of at least B*N complex values.
+// of at least min(B, apply_part_most(...))*N complex values: larger batches are applied in parts that
+// reuse it.
 // ---------------------------------------------------------------------------------------------
+int64_t apply_part_most(const Geo& g, int complex_bytes);
 hipError_t op_apply(const Geo& g, bool f64, int B, const Twiddles& tw, const void* f, const void* V,
                     void* out, void* tmp, double beta, double omega, bool nonlinear, hipStream_t s);
 

@@ -97,9 +97,11 @@ struct OpApply {
 // 138, 130.  32 x 640^2 FP64 302; 376, 302, 286.  256 x 256^2 FP32 145; 142, 130, 125.  Three-pass
 // (3-D) batches gain little (4 x 128^3 FP64 196; 212, 211, 187).
 constexpr int64_t kApplyPartBytes = int64_t(224) << 20;
+int64_t apply_part_most(const Geo& g, int complex_bytes) {
+    return std::max<int64_t>(1, kApplyPartBytes / (3 * (int64_t)complex_bytes * g.N));
+}
 static int apply_part(const Geo& g, int complex_bytes, int B) {
-    const int64_t field = 3 * (int64_t)complex_bytes * g.N;
-    const int64_t most = std::max<int64_t>(1, kApplyPartBytes / field);
+    const int64_t most = apply_part_most(g, complex_bytes);
     const int64_t parts = (B + most - 1) / most;
     return (int)((B + parts - 1) / parts);
 }
