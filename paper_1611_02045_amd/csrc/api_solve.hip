@@ -62,7 +62,6 @@ int run(BatchWork& w, int B, IterFields<T> f, std::vector<Scal>& hs, const gpe_p
     pa.refresh_every = o.refresh_every;
     pa.use_graph = o.use_graph != 0;
     pa.own_stream = w.own_stream;
-    pa.final_f_r_is_rp = false;
     HIPCHK(run_phase<T>(pa, f, hs, s));
     return GPE_OK;
 }
@@ -104,7 +103,6 @@ int profile_group(ProfileWork& w, int B, const gpe_problem_t* probs, bool in_f64
     pa.poll = nullptr;
     pa.check_every = 1;
     pa.refresh_every = 0;
-    pa.final_f_r_is_rp = false;
     KernelTimer timer;
     hipError_t e = timer.init();
     const bool fp32 = !in_f64 || o.precision == 1;
@@ -414,9 +412,13 @@ int run_concurrent(int n, hipStream_t s, F task) {
 // fill the chip: kernels of several streams share it but barely overlap in time while they leave it idle
 // (three grid groups that take 17.5, 10.2 and 7.0 ms alone took 34.7 ms side by side as six parts, 21.1 as
 // three).  Hence two parts for a call of one grid whose halves give every CU two workgroups, else one.
-// Per iteration, one batch against two parts (us): 8 x 512^2 FP64 192, 161; 16 x 512^2 FP32 185, 166;
-// 16 x 256^2 FP64 104, 96; 8 x 512^2 FP32 104, 107; 4 x 512^2 FP64 102, 98 (with the second part's set-up a
-// solve to 1e-8 takes 16.2 ms whole, 18.0 in parts).
+// Per iteration, one batch against two parts (us).  Beyond the line: 16 x 512^2 FP64 376, 335; 8 x 512^2 FP64 169,
+// 148; 32 x 256^2 FP64 158, 143; 16 x 512^2 FP32 175, 159; 8 x 512^2 FP32, on the line, 92, 87 (the second part's
+// set-up of 0.6 ms is won back by 90 iterations: 16 take 4.4 ms whole and 5.1 in parts, 96 take 12.6 and 12.3).
+// Before it: 16 x 256^2 FP64 85, 91; 4 x 512^2 FP64 96, 100; 8 x 256^2 FP64 48, 50.  Between one and two workgroups
+// per CU parts already win (6 x 512^2 FP64 129, 120; 24 x 256^2 FP64 121, 113), and on grids of 5 * 2^k points far
+// below the line (2 x 640^2 FP64, 96 iterations: 17.3 ms whole, 13.6 in parts, whose lone instances take the
+// 320-thread tile and absorb more rows): a better line is left to be drawn there.
 int solve_parts(int B, const gpe_problem_t& p, bool f32_fields, int groups) {
     if (B < 2 || groups > 1 || p.dim < 2) return 1;
     const Geo g = make_geo(p);

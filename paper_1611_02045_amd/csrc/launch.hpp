@@ -93,8 +93,9 @@ inline int pass_lines_rule(const Geo& g, int AX, int complex_bytes, int B) {
         // 320 threads when the launch has 32 such workgroups or more; with 16-byte points only up to one
         // per CU: their passes leave room for two or three waves per SIMD, where five-wave workgroups
         // pack worse than two of 160 threads.  Iteration at 640^2 (kernel time, us): one FP64 instance
-        // 120 -> 92, one FP32 100 -> 74; eight FP32 at 320^2 117 -> 94, at 640^2 258 -> 262; eight FP64
-        // (not taken) 465 -> 448 at 640^2, 151 -> 155 at 320^2, its y pass 45 -> 57.
+        // 120 -> 92, one FP32 100 -> 74.  Batches of eight, one rule for both sizes by point type: FP32 320^2
+        // 117 -> 94 against 640^2 258 -> 262 (taken), FP64 640^2 465 -> 448 against 320^2 151 -> 155, where
+        // the y pass went 45 -> 57 (not taken).
         C = kMaxPassThreads5 / TPL;
         const int64_t blocks = lines / C;
         if (valid_lines(g, AX, complex_bytes, C) && blocks >= 32 && (complex_bytes == 8 || blocks <= device_cus()))

@@ -154,8 +154,6 @@ __host__ __device__ inline size_t pass_lds_bytes(int M, int C, int threads, int 
     return b;
 }
 
-// Partial-sum buffers for reducing passes: parts[b][block][K] (FP64) and one ticket counter per
-// instance.  `nb` is the number of blocks per instance.
 // A region of per-block partial rows (K doubles each).  A producing pass writes its block blk of
 // instance b to row b * stride + off + blk (several passes can share a region, at different
 // offsets); a consumer reduces rows [b * stride, b * stride + nb).  stride 0 means nb.
@@ -167,8 +165,7 @@ struct Partials {
     __host__ __device__ int row_stride() const { return stride > 0 ? stride : nb; }
 };
 
-// Sum K partials of instance b over its nb blocks with all threads of the (last) block, in a
-// fixed order.  `red` is block_reduce scratch; `out` (LDS, K doubles) receives the totals.
+// Sum the K-sum rows of an instance's nb blocks with all threads of the consuming block, in a fixed order.  `red` is block_reduce scratch; `out` (LDS, K doubles) receives the totals.
 template <int K, unsigned MASK>
 __device__ __forceinline__ void reduce_partials(const double* parts, int nb, double* red, double* out) {
     double acc[K];

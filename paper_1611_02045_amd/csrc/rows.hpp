@@ -144,7 +144,7 @@ __global__ __launch_bounds__(256) void k_collapse(const double* parts, int nb, i
 }
 
 // Rows per instance up to which the consumers of a batch of B absorb a region as it is.  Every workgroup
-// of the consumer reads all of its instance's rows, where a collapse costs one launch of about 6 us: a lone
+// of the consumer reads all of its instance's rows, where a collapse costs one launch of 4.5 us and its gap: a lone
 // instance takes up to 512 rows (32 iterations, with collapse -> without, us: 640^2 FP64 4833 -> 4622, 1024 x
 // 512 FP64 4550 -> 4190, 64^3 unchanged), more instances, whose consumers have several workgroups per CU, 256
 // (eight FP64 at 640^2, 320 rows: 16250 collapsed, 16660 not).

@@ -5,7 +5,7 @@
 // stagnation of the residual, or a failed line search; then the iterate is promoted to FP64,
 // L phi is recomputed from it, the CG memory is reset and an FP64 phase finishes to tol.
 // Within a phase, iterations are queued in chunks of `check_every`; the host polls the
-// per-instance scalars between chunks (kernels of a finished instance return immediately).
+// per-instance scalars one chunk behind (kernels of a finished instance return immediately).
 // Every `refresh_every` iterations L phi and its scalars are recomputed from phi, bounding the
 // drift of the linearity update.  The reported E, lambda and ||r||_inf are recomputed in FP64
 // from the final iterate.
@@ -519,7 +519,6 @@ hipError_t run_phase(PhaseArgs& pa, IterFields<T> f, std::vector<Scal>& host_S, 
         graph.reset();
     }
     if ((e = hipStreamSynchronize(s)) != hipSuccess) return e;  // the chunk queued in vain
-    pa.final_f_r_is_rp = false;
     return hipSuccess;
 }
 

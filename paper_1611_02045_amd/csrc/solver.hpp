@@ -20,7 +20,6 @@ struct PhaseArgs {
     int refresh_every;
     bool own_stream = false; // the phase's stream may be captured (a non-blocking one of this library's)
     bool use_graph = false;  // replay chunks of check_every iterations as a captured graph
-    bool final_f_r_is_rp;
 };
 
 template <typename T>
