@@ -83,8 +83,21 @@ __host__ __device__ __forceinline__ void dft8(C2<T> (&v)[8]) {
     v[1] = b0; v[3] = b1; v[5] = b2; v[7] = b3;
 }
 
+// Products and sums with their roundings fixed: which of two products an addition fuses is the compiler's choice
+// else, and changes with the code around it.
 __host__ __device__ __forceinline__ float fma_of(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __host__ __device__ __forceinline__ double fma_of(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
+// a * b: a.y b.y and a.x b.y rounded, the other products fused.
+template <typename T>
+__host__ __device__ __forceinline__ C2<T> mul_fixed(C2<T> a, C2<T> b) {
+    return mk(fma_of(a.x, b.x, -(a.y * b.y)), fma_of(a.y, b.x, a.x * b.y));
+}
+// Re(conj(a) b) with the y product rounded (Y) or the x product.
+template <bool Y, typename T>
+__device__ __forceinline__ T redot_fixed(C2<T> a, C2<T> b) {
+    return Y ? fma_of(a.x, b.x, a.y * b.y) : fma_of(a.y, b.y, a.x * b.x);
+}
 
 // dft8 with the roundings of its outputs 3 and 7 fixed: the pair of twiddled differences b1 e^{..}, b3 e^{..}
 // enters their sum by a fused multiply-add and their difference as rounded products.  In dft8 itself the
@@ -260,7 +273,8 @@ __device__ __forceinline__ void fft_line(C2<T> (&v)[8], C2<T>* buf, const C2<T>*
 // wave.  CS > 0: point i of the line's LDS region sits at buf[i * CS] instead of the padded
 // buf[lpad(i)] (a column of a plane held in LDS, whose neighbouring columns go to neighbouring
 // lanes, so the stride needs no padding).  FIXED: the last stage is dft8_fixed (lines of 2^LG points).
-template <typename T, int DIR, int LG, bool WAVE, bool F5 = false, int CS = 0, bool FIXED = false>
+// FIXED_TW: a forward transform's products with twiddles from the table are mul_fixed.
+template <typename T, int DIR, int LG, bool WAVE, bool F5 = false, int CS = 0, bool FIXED = false, bool FIXED_TW = false>
 __device__ __forceinline__ void fft_line_ct(C2<T> (&v)[8], C2<T>* buf, const C2<T>* tw, int t) {
     static_assert(LG >= 3 && LG <= 10, "lines of 8 to 1024 points");
     static_assert(!F5 || (LG <= 7 && !WAVE), "lines of 5 * 2^LG points: at most 640, across waves");
@@ -314,10 +328,10 @@ __device__ __forceinline__ void fft_line_ct(C2<T> (&v)[8], C2<T>* buf, const C2<
                 w4.y = -w4.y;
             }
             const C2<T> w3 = mul(w1, w2);
-            v[1] = mul(v[1], w1);
-            v[2] = mul(v[2], w2);
+            v[1] = FIXED_TW && DIR < 0 ? mul_fixed(v[1], w1) : mul(v[1], w1);
+            v[2] = FIXED_TW && DIR < 0 ? mul_fixed(v[2], w2) : mul(v[2], w2);
             v[3] = mul(v[3], w3);
-            v[4] = mul(v[4], w4);
+            v[4] = FIXED_TW && DIR < 0 ? mul_fixed(v[4], w4) : mul(v[4], w4);
             v[5] = mul(v[5], mul(w1, w4));
             v[6] = mul(v[6], mul(w2, w4));
             v[7] = mul(v[7], mul(w3, w4));

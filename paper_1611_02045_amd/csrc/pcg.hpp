@@ -152,27 +152,34 @@ __device__ __forceinline__ void res_sums(double* acc, C2<T> r) {
     if (!isfinite(m2)) acc[A_NF] = 1.0;
 }
 
+// The inner products of the sums below: their roundings are the compiler's choice, or fixed (pcg_line.hip).
+struct FreeDots {
+    template <typename T> static __device__ __forceinline__ T dot(C2<T> a, C2<T> b) { return redot(a, b); }
+    template <typename T> static __device__ __forceinline__ T dot_lp(C2<T> a, C2<T> lp) { return redot(a, lp); }
+    template <typename T> static __device__ __forceinline__ T phi2(C2<T> ph) { return abs2(ph); }
+};
+
 // (OFF: the entry that acc[0] stands for)
-template <typename T, int OFF = 0>
+template <typename T, int OFF = 0, class D = FreeDots>
 __device__ __forceinline__ void cg_sums(double* acc, C2<T> r, C2<T> pr, C2<T> rp, C2<T> pp, C2<T> ph) {
-    acc[A_RPR - OFF] += (double)redot(r, pr);
-    acc[A_RPPR - OFF] += (double)redot(rp, pr);
-    acc[A_PRPHI - OFF] += (double)redot(pr, ph);
-    acc[A_PRPR - OFF] += (double)abs2(pr);
-    acc[A_PRPP - OFF] += (double)redot(pr, pp);
-    acc[A_RPP - OFF] += (double)redot(r, pp);
-    acc[A_PPPHI - OFF] += (double)redot(pp, ph);
-    acc[A_PPPP - OFF] += (double)abs2(pp);
-    acc[A_RPHI - OFF] += (double)redot(r, ph);
-    acc[A_PHIPHI - OFF] += (double)abs2(ph);
+    acc[A_RPR - OFF] += (double)D::dot(r, pr);
+    acc[A_RPPR - OFF] += (double)D::dot(rp, pr);
+    acc[A_PRPHI - OFF] += (double)D::dot(pr, ph);
+    acc[A_PRPR - OFF] += (double)D::dot(pr, pr);
+    acc[A_PRPP - OFF] += (double)D::dot(pr, pp);
+    acc[A_RPP - OFF] += (double)D::dot(r, pp);
+    acc[A_PPPHI - OFF] += (double)D::dot(pp, ph);
+    acc[A_PPPP - OFF] += (double)D::dot(pp, pp);
+    acc[A_RPHI - OFF] += (double)D::dot(r, ph);
+    acc[A_PHIPHI - OFF] += (double)D::phi2(ph);
 }
 
 // Line-search sums at one point (A = |phi|^2, B = Re conj(phi) phat, C = |phat|^2; o = L phat).
-template <typename T, int OFF = 0>
+template <typename T, int OFF = 0, class D = FreeDots>
 __device__ __forceinline__ void linesearch_sums(double* acc, C2<T> ph, C2<T> p, C2<T> o) {
-    const double A = abs2(ph), Bq = redot(ph, p), Cq = abs2(p);
-    acc[B_C - OFF] += (double)redot(p, o);
-    acc[B_B - OFF] += (double)redot(ph, o);
+    const double A = D::dot(ph, ph), Bq = D::dot(ph, p), Cq = D::dot(p, p);
+    acc[B_C - OFF] += (double)D::dot_lp(p, o);
+    acc[B_B - OFF] += (double)D::dot_lp(ph, o);
     acc[B_AA - OFF] += A * A;
     acc[B_AB - OFF] += A * Bq;
     acc[B_ACA - OFF] += A * (Cq - A);

@@ -6,16 +6,29 @@
 // direction, L phat and the line-search sums, as in pcg_passes.hpp, with the same scalar logic) and
 // touches global memory only when it starts and ends.  What bounds an iteration is the chain of one or two
 // waves: as two launches, with the state's trips through memory and two row reductions, it took 25 us at
-// 256 points in FP64; the solve of that line to 1e-10 (57 iterations) went from 1771 us to 676.
+// 256 points in FP64; the solve of that line to 1e-10 (57 iterations) went from 1673 us to 596.
+//
+// Element by element the arithmetic is that of the two launches: which product of a sum is rounded and which
+// fused is written out wherever the compiler chose otherwise in this kernel than in those, so that FP32 solves
+// return the same bits (the transform of the scaled residual starts in the block that scales it, as there, hence
+// the compile-time SPECTRAL).
 #include "pcg_passes.hpp"
 
 namespace gpe {
 
-// The line transform for a compile-time size (LG), else the run-time one.
-template <typename T, int DIR, int LG>
+// The sums' inner products; LG 0: the run-time size.
+template <int LG>
+struct LineDots {
+    template <typename T> static __device__ __forceinline__ T dot(C2<T> a, C2<T> b) { return redot_fixed<true>(a, b); }
+    template <typename T> static __device__ __forceinline__ T dot_lp(C2<T> a, C2<T> lp) { return redot_fixed<LG != 0>(a, lp); }
+    template <typename T> static __device__ __forceinline__ T phi2(C2<T> ph) { return redot_fixed<false>(ph, ph); }
+};
+
+// The line transform for a compile-time size (LG, see ct_points), else the run-time one.
+template <typename T, int DIR, int LG, bool FIXED = false>
 __device__ __forceinline__ void line_fft1(C2<T> (&v)[8], C2<T>* buf, const C2<T>* tw, int t, int lg, int M, bool wave) {
     if constexpr (LG > 0)
-        fft_line_ct<T, DIR, LG, LG <= 9>(v, buf, tw, t);
+        fft_line_ct<T, DIR, ct_lg(LG), !ct_f5(LG) && ct_lg(LG) <= 9, ct_f5(LG), 0, FIXED, true>(v, buf, tw, t);
     else
         fft_line<T, DIR>(v, buf, tw, t, lg, M, wave);
 }
@@ -29,16 +42,16 @@ inline size_t line_lds(const Geo& g, size_t point) {
     return point * ((size_t)g.n[0] + (size_t)lines * line_stride(g.n[0])) + 16;
 }
 
-template <typename T, int LG>
+template <typename T, int LG, bool SPECTRAL>
 __global__ __launch_bounds__(128) void k_pcg_line(IterFields<T> f, Geo g, const C2<T>* __restrict__ twg, Scal* S,
-                                                 double* rows, int row_stride, int iters, int spectral, int pre,
+                                                 double* rows, int row_stride, int iters, int pre,
                                                  int post) {
     extern __shared__ double4 smem_raw[];
     __shared__ double red[(128 / 64 + 1) * 16 + 4];
     __shared__ double tot_a[A_K], tot_b[B_K];
     __shared__ Scal s_local;
     Scal& s = s_local;
-    const int lg = LG > 0 ? LG : g.lg[0], M = g.n[0], TPL = M >> 3;
+    const int lg = LG > 0 ? ct_lg(LG) : g.lg[0], M = LG > 0 ? ct_points(LG) : g.n[0], TPL = M >> 3;
     const int b = g.imap ? g.imap[blockIdx.x] : g.b0 + (int)blockIdx.x;
     C2<T>* tw = reinterpret_cast<C2<T>*>(smem_raw);
     const int c = threadIdx.x / TPL, t = threadIdx.x - c * TPL;
@@ -91,9 +104,9 @@ __global__ __launch_bounds__(128) void k_pcg_line(IterFields<T> f, Geo g, const 
                     acc[A_DPHI] = fmax(acc[A_DPHI], (double)abs2(sub(np, ph[q])));
                     ph[q] = np;
                 }
-                const T rho = abs2(ph[q]);
+                const T rho = LineDots<LG>::phi2(ph[q]);
                 const double r2 = rho;
-                acc[A_A] += (double)redot(ph[q], lph[q]);
+                acc[A_A] += (double)redot_fixed<false>(ph[q], lph[q]);
                 acc[A_Q4] += r2 * r2;
                 acc[A_N2] += r2;
                 r[q] = add(lph[q], scl(ph[q], beta * rho - lam));
@@ -102,7 +115,7 @@ __global__ __launch_bounds__(128) void k_pcg_line(IterFields<T> f, Geo g, const 
                 v[q] = scl(r[q], pscale<T>(pre, d[q]));
             }
         }
-        if (spectral) {
+        if constexpr (SPECTRAL) {
             line_fft1<T, -1, LG>(v, buf, tw, t, lg, M, wave);
             const double invN = 1.0 / M;
 #pragma unroll
@@ -110,12 +123,12 @@ __global__ __launch_bounds__(128) void k_pcg_line(IterFields<T> f, Geo g, const 
                 const double k = freq_of(t + q * TPL, M, s.dk[0]);
                 v[q] = scl(v[q], (T)(invN / (s.lamt + 0.5 * k * k)));
             }
-            line_fft1<T, +1, LG>(v, buf, tw, t, lg, M, wave);
+            line_fft1<T, +1, LG, true>(v, buf, tw, t, lg, M, wave);
         }
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             v[q] = on ? scl(v[q], pscale<T>(post, d[q])) : zero;  // P r
-            cg_sums<T>(acc, r[q], v[q], rp[q], pp[q], ph[q]);
+            cg_sums<T, 0, LineDots<LG>>(acc, r[q], v[q], rp[q], pp[q], ph[q]);
         }
         block_reduce<A_K, A_MAXMASK>(acc, red, tot_a);
         finish<A_K>(&s, tot_a, 0, [](Scal& S1, const double* tt) {
@@ -150,7 +163,7 @@ __global__ __launch_bounds__(128) void k_pcg_line(IterFields<T> f, Geo g, const 
         for (int q = 0; q < 8; ++q) {
             const C2<T> o = on ? add(v[q], scl(u[q], V[q])) : zero;
             lp[q] = o;
-            linesearch_sums<T>(bs, ph[q], u[q], o);
+            linesearch_sums<T, 0, LineDots<LG>>(bs, ph[q], u[q], o);
         }
         block_reduce<B_K, B_MAXMASK>(bs, red, tot_b);
     }
@@ -180,13 +193,19 @@ hipError_t enqueue_line(const IterCtx<T>& c, int iters, hipStream_t s) {
     const int Bl = g.bl > 0 ? g.bl : c.B;
     const LaunchEvents* ev =
         c.timer ? c.timer->next("pcg_iteration_x", 21.0 * (double)sizeof(T) * (double)g.N * (double)c.B) : nullptr;
-    using K = decltype(&k_pcg_line<T, 0>);
-    const K variants[5] = {k_pcg_line<T, 0>, k_pcg_line<T, 6>, k_pcg_line<T, 7>, k_pcg_line<T, 8>, k_pcg_line<T, 9>};
+    // compile-time transforms at the sizes where the passes have them (640 points, 24 FP32 iterations with the
+    // combined preconditioner: 740 us with the run-time one, 628)
+    using K = decltype(&k_pcg_line<T, 0, true>);
+    const K variants[2][6] = {
+        {k_pcg_line<T, 0, false>, k_pcg_line<T, 6, false>, k_pcg_line<T, 7, false>, k_pcg_line<T, 8, false>,
+         k_pcg_line<T, 9, false>, k_pcg_line<T, 107, false>},
+        {k_pcg_line<T, 0, true>, k_pcg_line<T, 6, true>, k_pcg_line<T, 7, true>, k_pcg_line<T, 8, true>,
+         k_pcg_line<T, 9, true>, k_pcg_line<T, 107, true>}};
     const int lg = g.lg[0];
-    const K kern = variants[!g.f5[0] && lg >= 6 && lg <= 9 ? lg - 5 : 0];
+    const K kern = variants[spectral ? 1 : 0][g.f5[0] ? (lg == 7 ? 5 : 0) : lg >= 6 && lg <= 9 ? lg - 5 : 0];
     launch_timed(ev, kern, dim3((unsigned)Bl), dim3((unsigned)line_threads(g)), line_lds(g, sizeof(C2<T>)), s, c.f, g,
                  (const C2<T>*)c.tw->get(0, sizeof(T) == 8), c.S + c.B,
-                 c.parts + (size_t)R_B * c.region_doubles, (int)B_K, iters, spectral ? 1 : 0, pre, post);
+                 c.parts + (size_t)R_B * c.region_doubles, (int)B_K, iters, pre, post);
     return hipGetLastError();
 }
 
