@@ -183,7 +183,7 @@ def cpu_all_cores(prob, V, starts, iters, gpu_fp64_iters):
 
 
 def cpu_baseline(prob, V, phi0, iters, gpu_fp64_iters_total):
-    """The FP64 oracle, as it stands, on the GPU box's host: PCG iterations/s and H_phi applies/s on
+    """The FP64 oracle, as it stands, on the GPU machine's host: PCG iterations/s and H_phi applies/s on
     the 512^2 workload (bounded samples), the 1-D 256-point configuration solved to 1e-10 and the
     2-D 256^2 and 3-D 128^3 configurations sampled, all on one thread (numpy's transforms are
     single-threaded; BLAS is held to one thread so that the figure does not depend on the box's
