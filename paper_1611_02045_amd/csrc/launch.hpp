@@ -84,12 +84,12 @@ inline int floor_pow2(int x) {
     return p;
 }
 
-inline int pass_lines_rule(const Geo& g, int AX, int complex_bytes, int B) {
+inline int pass_lines_rule(const Geo& g, int AX, int complex_bytes, int B, bool wide = true) {
     const int TPL = g.n[AX] / 8;
     const int64_t lpf = lines_per_field(g, AX);
     const int64_t lines = lpf * (int64_t)B;
     int C;
-    if (g.f5[AX]) {
+    if (wide && g.f5[AX]) {
         // 320 threads when the launch has 32 such workgroups or more; with 16-byte points only up to one
         // per CU: their passes leave room for two or three waves per SIMD, where five-wave workgroups
         // pack worse than two of 160 threads.  Iteration at 640^2 (kernel time, us): one FP64 instance

@@ -36,6 +36,7 @@ struct LineCtx {
     const Scal* sc; // the instance's scalar state in LDS (PCG passes only)
     const LinS* ls; // the same of the linear solvers' passes
     bool wave;      // every line of the workgroup lies within one wave (x passes, M <= 512)
+    bool wide;      // compile time: 320-thread workgroups with the run-time-size transform
     __device__ __forceinline__ int64_t at(int s) const { return base + (int64_t)(t + s * TPL) * stride; }
     __device__ __forceinline__ int k(int s) const { return t + s * TPL; }
 };
@@ -282,6 +283,7 @@ void pass_kernel(Geo g, int C, const C2<T>* __restrict__ twg, Op op, Partials pr
     extern __shared__ double4 smem_raw[];
     int blk_in_inst;
     LineCtx lc = decode_line<AX, LG>(g, C, blk_in_inst);
+    lc.wide = MAXT > 256 && LG == 0;
     C2<T>* tw = reinterpret_cast<C2<T>*>(smem_raw);
     constexpr int kPB = (int)sizeof(C2<T>);
     const int stride_pts = line_stride(lc.M, kPB, AX, C);

@@ -128,12 +128,19 @@ hipError_t enqueue_iteration(const IterCtx<T>& c, hipStream_t s) {
     }
     const Partials pdir = consumable(pa, R_AC, A_K);
     // ---- phase B ----
+    // Whether 256-thread workgroups of a pass over half of the batch would be one per CU or fewer.  Such launches
+    // have the form for few workgroups, which rounds the x product of <phat, L phat> and <phi, L phat> where the others
+    // round the y product; the 320-thread form, which has both kinds, rounds as they did.
+    auto few_blocks = [&](int ax) {
+        const int64_t half = c.B - c.B / 2;
+        return lines_per_field(g, ax) / pass_lines_rule(g, ax, cb, (int)half, false) * half <= device_cus();
+    };
     if (g.dim == 2) {
         OpLp<T, 0, true, false> ox{f, S_step, S_dir, pdir};
         if ((e = launch_pass<T, 0>(g, c.B, c.tw->get(0, f64), ox, pb0, s,
                 tick("test_dir_Lp_x", 11))) != hipSuccess)
             return e;
-        OpLp<T, 1, false, true> oy{f, S_dir, nullptr, none};
+        OpLp<T, 1, false, true> oy{f, S_dir, nullptr, none, few_blocks(1)};
         if ((e = launch_pass<T, 1>(g, c.B, c.tw->get(1, f64), oy, pb1, s,
                 tick("Lp_y_linesearch", 8))) != hipSuccess)
             return e;
@@ -144,7 +151,7 @@ hipError_t enqueue_iteration(const IterCtx<T>& c, hipStream_t s) {
             return e;
         OpLp<T, 1, false, false> oy{f, S_dir, nullptr, none};
         if ((e = launch_pass<T, 1>(g, c.B, c.tw->get(1, f64), oy, pb1, s, tick("Lp_y", 8))) != hipSuccess) return e;
-        OpLp<T, 2, false, true> oz{f, S_dir, nullptr, none};
+        OpLp<T, 2, false, true> oz{f, S_dir, nullptr, none, few_blocks(2)};
         if ((e = launch_pass<T, 2>(g, c.B, c.tw->get(2, f64), oz, pb2, s,
                 tick("Lp_z_linesearch", 8))) != hipSuccess)
             return e;

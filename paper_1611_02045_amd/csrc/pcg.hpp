@@ -159,6 +159,14 @@ struct FreeDots {
     template <typename T> static __device__ __forceinline__ T phi2(C2<T> ph) { return abs2(ph); }
 };
 
+// The y product rounded, but |phi|^2's x product and, with LP_X, that of the sums with L phat.
+template <bool LP_X>
+struct FixedDots {
+    template <typename T> static __device__ __forceinline__ T dot(C2<T> a, C2<T> b) { return redot_fixed<true>(a, b); }
+    template <typename T> static __device__ __forceinline__ T dot_lp(C2<T> a, C2<T> lp) { return redot_fixed<!LP_X>(a, lp); }
+    template <typename T> static __device__ __forceinline__ T phi2(C2<T> ph) { return redot_fixed<false>(ph, ph); }
+};
+
 // (OFF: the entry that acc[0] stands for)
 template <typename T, int OFF = 0, class D = FreeDots>
 __device__ __forceinline__ void cg_sums(double* acc, C2<T> r, C2<T> pr, C2<T> rp, C2<T> pp, C2<T> ph) {

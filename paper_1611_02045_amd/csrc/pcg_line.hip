@@ -16,14 +16,6 @@
 
 namespace gpe {
 
-// The sums' inner products; LG 0: the run-time size.
-template <int LG>
-struct LineDots {
-    template <typename T> static __device__ __forceinline__ T dot(C2<T> a, C2<T> b) { return redot_fixed<true>(a, b); }
-    template <typename T> static __device__ __forceinline__ T dot_lp(C2<T> a, C2<T> lp) { return redot_fixed<LG != 0>(a, lp); }
-    template <typename T> static __device__ __forceinline__ T phi2(C2<T> ph) { return redot_fixed<false>(ph, ph); }
-};
-
 // The line transform for a compile-time size (LG, see ct_points), else the run-time one.
 template <typename T, int DIR, int LG, bool FIXED = false>
 __device__ __forceinline__ void line_fft1(C2<T> (&v)[8], C2<T>* buf, const C2<T>* tw, int t, int lg, int M, bool wave) {
@@ -104,7 +96,7 @@ __global__ __launch_bounds__(128) void k_pcg_line(IterFields<T> f, Geo g, const 
                     acc[A_DPHI] = fmax(acc[A_DPHI], (double)abs2(sub(np, ph[q])));
                     ph[q] = np;
                 }
-                const T rho = LineDots<LG>::phi2(ph[q]);
+                const T rho = FixedDots<LG == 0>::phi2(ph[q]);
                 const double r2 = rho;
                 acc[A_A] += (double)redot_fixed<false>(ph[q], lph[q]);
                 acc[A_Q4] += r2 * r2;
@@ -128,7 +120,7 @@ __global__ __launch_bounds__(128) void k_pcg_line(IterFields<T> f, Geo g, const 
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
             v[q] = on ? scl(v[q], pscale<T>(post, d[q])) : zero;  // P r
-            cg_sums<T, 0, LineDots<LG>>(acc, r[q], v[q], rp[q], pp[q], ph[q]);
+            cg_sums<T, 0, FixedDots<LG == 0>>(acc, r[q], v[q], rp[q], pp[q], ph[q]);
         }
         block_reduce<A_K, A_MAXMASK>(acc, red, tot_a);
         finish<A_K>(&s, tot_a, 0, [](Scal& S1, const double* tt) {
@@ -163,7 +155,7 @@ __global__ __launch_bounds__(128) void k_pcg_line(IterFields<T> f, Geo g, const 
         for (int q = 0; q < 8; ++q) {
             const C2<T> o = on ? add(v[q], scl(u[q], V[q])) : zero;
             lp[q] = o;
-            linesearch_sums<T, 0, LineDots<LG>>(bs, ph[q], u[q], o);
+            linesearch_sums<T, 0, FixedDots<LG == 0>>(bs, ph[q], u[q], o);
         }
         block_reduce<B_K, B_MAXMASK>(bs, red, tot_b);
     }

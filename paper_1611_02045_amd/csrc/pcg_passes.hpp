@@ -712,6 +712,7 @@ struct OpLp {
     const Scal* Sin;   // FIRST: S_step; otherwise S_dir
     Scal* Sout;        // FIRST: S_dir
     Partials pdir;     // FIRST: the phase-A sums
+    bool few = false;  // LAST: see few_blocks
     using Intake = std::conditional_t<FIRST, IntakeA, IntakeState>;
     __device__ void intake(int b, int, Intake& it) const {
         it.st.issue(Sin, b);
@@ -813,7 +814,10 @@ struct OpLp {
                 f.w[i] = o;
             } else {
                 f.lp[i] = o;
-                linesearch_sums<T, ROW_AT>(acc, st.ph[q], st.p[q], o);
+                if (sizeof(T) == 4 && lc.wide && few)
+                    linesearch_sums<T, ROW_AT, FixedDots<true>>(acc, st.ph[q], st.p[q], o);
+                else
+                    linesearch_sums<T, ROW_AT>(acc, st.ph[q], st.p[q], o);
             }
         }
     }
