@@ -814,8 +814,8 @@ struct OpLp {
                 f.w[i] = o;
             } else {
                 f.lp[i] = o;
-                if (sizeof(T) == 4 && lc.wide && few)
-                    linesearch_sums<T, ROW_AT, FixedDots<true>>(acc, st.ph[q], st.p[q], o);
+                if (sizeof(T) == 4 && lc.wide)
+                    linesearch_sums<T, ROW_AT>(acc, st.ph[q], st.p[q], o, PickDots{few});
                 else
                     linesearch_sums<T, ROW_AT>(acc, st.ph[q], st.p[q], o);
             }
